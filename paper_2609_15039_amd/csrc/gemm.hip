@@ -441,15 +441,16 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride,
     // (consecutive MFMAs on one accumulator would wait for each other's results).
     // The loads of the tile D ahead (slot nq) are issued a quarter per k step,
     // interleaved with the MFMAs, so the matrix cores keep working while they issue.
-    auto compute = [&](int t, auto sc, auto nsc) {
+    auto compute = [&](int t, auto sc, auto nsc, auto ahead) {
         constexpr int q = decltype(sc)::value;
+        constexpr bool AHEAD = decltype(ahead)::value;
         const unsigned char* sb = stage(sc);
         bf16x8_t a[2][NPL][TM];
         read_a(sb, 0, a[0]);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             if (s + 1 < 4) read_a(sb, s + 1, a[(s + 1) & 1]);
-            issue_part(t + D, nsc, s);
+            if constexpr (AHEAD) issue_part(t + D, nsc, s);
 #pragma unroll
             for (int p = 0; p < NPL; ++p)
 #pragma unroll
@@ -459,10 +460,12 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride,
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s & 1][p][i], as_bf16x8(wb[q][j][s]), acc[i][j], 0, 0, 0);
             // one group: this step's fragment reads first, then MFMAs with the loads in between
             __builtin_amdgcn_sched_group_barrier(0x100, NPL * TM, 0);
+            if constexpr (AHEAD) {
 #pragma unroll
-            for (int g = 0; g < (LA + 3) / 4 + TN; ++g) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                for (int g = 0; g < (LA + 3) / 4 + TN; ++g) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                }
             }
             __builtin_amdgcn_sched_group_barrier(0x008, NPL * TM * TN, 0);
             __builtin_amdgcn_sched_barrier(0);
@@ -475,7 +478,19 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride,
         constexpr int q = decltype(sc)::value;
         wait_vmem<(D - 1) * (LA + LW)>();
         __builtin_amdgcn_s_barrier();
-        compute(t, sc, std::integral_constant<int, (q + D) % S>{});
+        compute(t, sc, std::integral_constant<int, (q + D) % S>{}, std::true_type{});
+    };
+    // tile I of the last, partial turn (I < S - 1 = D): nothing more is issued, so the tiles in
+    // flight behind it are those up to the turn's tile D - 1.  (Issuing the tiles past the split's
+    // last one here, as the loop does, left the count of loads behind this tile to the compiler: it
+    // dropped the W loads nobody reads and kept the masked-input ones, the wait of the second and
+    // later tiles of the turn was then too weak, and the last tiles could be multiplied before the
+    // other waves' masked input had landed.)
+    auto last_step = [&](int t, auto sc) {
+        constexpr int I = decltype(sc)::value;
+        wait_vmem<(D - 1 - I) * (LA + LW)>();
+        __builtin_amdgcn_s_barrier();
+        compute(t, sc, sc, std::false_type{});
     };
 
     issue(0, std::integral_constant<int, 0>{});
@@ -489,9 +504,9 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride,
         if constexpr (S > 3) step(t + 3, std::integral_constant<int, 3>{});
     }
     // the last, partial turn: at most S - 1 tiles, the same count for every wave
-    if (t < nk) step(t, std::integral_constant<int, 0>{});
-    if constexpr (S > 2) if (t + 1 < nk) step(t + 1, std::integral_constant<int, 1>{});
-    if constexpr (S > 3) if (t + 2 < nk) step(t + 2, std::integral_constant<int, 2>{});
+    if (t < nk) last_step(t, std::integral_constant<int, 0>{});
+    if constexpr (S > 2) if (t + 1 < nk) last_step(t + 1, std::integral_constant<int, 1>{});
+    if constexpr (S > 3) if (t + 2 < nk) last_step(t + 2, std::integral_constant<int, 2>{});
     wait_vmem<0>(); // the loads issued past the last tile (zeros) have landed before the workgroup ends
 
     if (ksplit == 1) {
