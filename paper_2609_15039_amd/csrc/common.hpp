@@ -110,6 +110,14 @@ size_t skinny_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_t
 int launch_skinny(const void* A, int prec, int64_t lda, int64_t plane_stride, const void* W, int w_type,
                   int64_t ldw, const float* C, int64_t ldc, float* Out, int64_t ldo, int64_t M,
                   int64_t N, int64_t K, void* ws, size_t ws_bytes, hipStream_t s);
+// bfloat16 GEMM for few tokens whose K is split over the waves of a workgroup: no workspace.
+struct WsplitPlan {
+    int tn;      // 16-column blocks of a workgroup
+    double cost; // microseconds per 64-k tile
+};
+WsplitPlan plan_wsplit(int64_t M, int64_t N, int prec, int w_type);
+int launch_wsplit(const void* A, int prec, int64_t lda, int64_t plane_stride, const void* W, int w_type, int64_t ldw,
+                  const float* C, int64_t ldc, float* Out, int64_t ldo, int64_t M, int64_t N, int64_t K, hipStream_t s);
 // bfloat16 W (N x K, row-major) -> the tiled order (splitee_tile_weights).
 int launch_tile_weights(const uint16_t* W, int64_t ldw, int64_t N, int64_t K, uint16_t* Wt, hipStream_t s);
 // Binary64 GEMM Out = A W^T (- C), A binary64, W bf16 / f32, Out binary64 or rounded to binary32.

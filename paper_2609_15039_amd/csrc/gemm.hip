@@ -17,17 +17,12 @@
 // M), each writes its float32 partial tile to the workspace and the last one to
 // arrive (device-scope counter) sums the partials in split order and applies
 // the epilogue, so results do not depend on arrival order.
-#include "common.hpp"
+#include "gemm_dev.hpp"
 
 #include <algorithm>
 #include <type_traits>
 
 namespace {
-
-constexpr int WAVE = 64;
-typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ bf16x8_t as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8_t, v); }
 
 // Split-K hand-off between the workgroups of one output tile.  Partials are
 // written with agent-scope relaxed atomic stores (or sc1 buffer stores) and read
@@ -199,26 +194,6 @@ __device__ __forceinline__ void finish_tile(const f32x4_t (&acc)[TM][TN], float*
     if (tid == 0) splitk_reset(counters + tile);
 }
 
-// ------------------------------------------------- bounds-checked buffer loads
-// Operands are read with buffer loads whose resource covers exactly the matrix:
-// a lane whose row or k lies outside it gets an offset beyond the extent and
-// reads zeros, which pads every tail.  A bfloat16 K tile is 64 k = 8 units of 16
-// bytes per row.
-
-constexpr int BK = 64;
-constexpr uint32_t OOB = 0x80000000u;
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
-}
-
-__device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t r, uint32_t voff)
-{
-    u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0);
-    return make_uint4(v.x, v.y, v.z, v.w);
-}
-
 // ----------------------------------------------- bf16 MFMA, W streamed (M > 16)
 // For weight-streaming shapes W is the only large operand and is read once: each
 // wave loads its own WN columns of W from HBM straight into MFMA B-operand
@@ -241,21 +216,11 @@ __device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t r, uint32_t voff)
 // 1 KB the 64 lanes load, so every load is 8 whole lines.  With tiled W the kernel
 // runs 8 waves (two per SIMD): one wave's MFMAs overlap the other's load issue.
 
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
 template <int I, int BYTES>
 __device__ __forceinline__ unsigned char* stream_stage()
 {
     __shared__ __attribute__((aligned(16))) unsigned char buf[BYTES];
     return buf;
-}
-
-// waits until at most N of this wave's vector-memory operations are outstanding
-template <int N>
-__device__ __forceinline__ void wait_vmem()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 constexpr int ST_NW = 4; // waves per workgroup of the streamed kernel (WGM x WGN)
@@ -963,35 +928,12 @@ constexpr int SK_LDS_MAX = 64 * 1024; // masked-input slice per workgroup (two w
 constexpr int SK_TARGET_WGS = 512;
 constexpr int SK_CP = SK_LDS_MAX / 16 / 256; // slice units per thread (16 at 64 KB)
 
-// Where the skinny kernel's masked input comes from: NPL bfloat16 planes A
-// (plane p at A + p * pstride), or (MASK) float32 X and mask eta, from which the
-// kernel forms fl32(X + eta) and its planes itself.
-struct SkSrc {
-    const uint16_t* A; int64_t lda, pstride;
-    const float* X; int64_t ldx;
-    const float* eta; int64_t ld_eta;
-};
-
 // Masked-input units (8 float32 of X and of eta) per thread per load round of the skinny
 // kernel when it forms the mask: 2 up to 8 rows, 4 above, so that at 16 rows and 16 k steps
 // per split the whole slice is requested before the W ring (a round issued after the ring
 // waits for all of it, since a wave's loads complete in order).  Measured on the Qwen3-4B
 // projections: 4 per round made 16 rows 4.8% faster and 4 rows 3.7% slower.
 constexpr int SK_MCP_SMALL = 2, SK_MCP_LARGE = 4;
-
-template <int NPL>
-__device__ __forceinline__ void planes_of(const float (&x)[8], uint4 (&q)[NPL])
-{
-#pragma unroll
-    for (int h = 0; h < 4; ++h) {
-        if (NPL == 1) {
-            reinterpret_cast<uint32_t*>(&q[0])[h] = splitee::bf16x2_rne(x[2 * h], x[2 * h + 1]);
-        } else {
-            splitee::split3_bf16x2(x[2 * h], x[2 * h + 1], reinterpret_cast<uint32_t*>(&q[0])[h],
-                                   reinterpret_cast<uint32_t*>(&q[1])[h], reinterpret_cast<uint32_t*>(&q[2])[h]);
-        }
-    }
-}
 
 template <int NPL, int R, bool MASK, bool TILED = false, int MCP = SK_MCP_SMALL>
 __global__ void __launch_bounds__(256)
@@ -1843,6 +1785,19 @@ Plan plan_stream(int64_t M, int64_t N, int64_t K, int prec, int w_type, bool all
     return p;
 }
 
+// Above this many rows the tiles of the streamed kernel outnumber the CUs on any projection.
+constexpr int64_t WSPLIT_MAX_M = 128;
+
+// Microseconds per K tile of the streamed kernel with K unsplit: rounds of 256 workgroups
+// times a tile's time, to compare with plan_wsplit (both fitted to 4-64 tokens on the
+// Llama-3.2-3B and Qwen3-4B projections, tiled W: a 128-column tile takes 0.65-0.8 us with three
+// planes and 0.5 with one, a 256-column tile 1.0-1.1 and 0.8).
+double unsplit_cost(const Plan& p, int prec)
+{
+    const double tile = (prec == SPLITEE_PREC_BF16X3 ? 1.05 : 0.8) * (p.bn >= 192 ? 1.0 : 0.7);
+    return (double)(((int64_t)p.mtiles * p.ntiles + 255) / 256) * tile;
+}
+
 Plan plan_tiled(int64_t M, int64_t N, int64_t K, int prec, int w_type, bool allow_split)
 {
     if (use_stream(prec, w_type)) return plan_stream(M, N, K, prec, w_type, allow_split);
@@ -2093,6 +2048,13 @@ int launch_gemm(const void* A, int prec, int64_t lda, int64_t pstride, const voi
         if ((planes - 1) * pstride * 2 + M * lda * 2 >= (int64_t(1) << 31) || wbytes >= (int64_t(1) << 31) ||
             p.part_bytes >= (size_t(1) << 31))
             return SPLITEE_ERR_UNSUPPORTED;
+        if (!allow_split) { // splitee_masked_linear: no workspace
+            const SkSrc src{a, lda, pstride, nullptr, 0, nullptr, 0};
+            if (M <= GV_MMAX && w_type == SPLITEE_BF16 && M * K * 4 <= 160 * 1024)
+                return launch_gemv<false>(src, prec, W, ldw, C, ldc, Out, ldo, M, N, K, s);
+            if (M <= WSPLIT_MAX_M && plan_wsplit(M, N, prec, w_type).cost < unsplit_cost(p, prec))
+                return launch_wsplit(A, prec, lda, pstride, W, w_type, ldw, C, ldc, Out, ldo, M, N, K, s);
+        }
         float* pp = reinterpret_cast<float*>(ws);
 #define ST_LAUNCH(NP, BM_, BN_, WGM_, D_, NW_, T_) hipLaunchKernelGGL((gemm_stream_kernel<NP, BM_, BN_, WGM_, D_, NW_, T_>), grid, dim3(NW_ * WAVE), 0, s, a, lda, pstride, w, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, pp)
 #define ST_SUM(BM_, BN_, WGM_, WGN_) hipLaunchKernelGGL((stream_sum_kernel<BM_, BN_, WGM_, WGN_>), g2, dim3(256), 0, s, pp, p.ksplit, C, ldc, Out, ldo, m, n, p.mtiles, tiles)
