@@ -354,28 +354,31 @@ gemm_stream_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride,
 
     uint4 wb[S][TN][4];
     // part `part` (0..3) of the loads of relative tile t into ring slot q: W of k step
-    // `part` and a quarter of the masked-input DMA (the remainder with the last part)
+    // `part` and a quarter of the masked-input DMA (the remainder with the last part).  An
+    // offset at or past OOB stays there whatever k adds (the matrices are below 2 GB), so a load
+    // past an edge needs a select at most: a branch around it would end the block in which
+    // the loads are spread between the MFMAs
     constexpr int LA4 = LA / 4;
     auto issue_part = [&](int t, auto sc, int part) {
         constexpr int q = decltype(sc)::value;
         const int kt = kt0 + t, kb = kt * BK;
-        const bool live = kt < kt1;
+        const uint32_t dead = kt < kt1 ? 0u : OOB;
         unsigned char* sb = stage(sc);
         const int i0 = part * LA4, i1 = part == 3 ? LA : i0 + LA4;
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             if (i < i0 || i >= i1) continue;
-            const uint32_t off = (live && aoff[i] != OOB && kb + akc[i] < K) ? aoff[i] + (uint32_t)kb * 2 : OOB;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(sb + (wave + NW * i) * 1024), 16, (int)off, 0, 0, 0);
+            const uint32_t off = (aoff[i] + (uint32_t)kb * 2) | dead;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr_t)(sb + (wave + NW * i) * 1024), 16,
+                                                     (int)(kb + akc[i] < K ? off : OOB), 0, 0, 0);
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             if (TILED) { // k past K is zero padding of the tiled layout
-                const bool ok = live && woff[j] != OOB;
-                wb[q][j][part] = load16(rw, ok ? woff[j] + (uint32_t)(kt * 4 + part) * 1024 : OOB);
+                wb[q][j][part] = load16(rw, (woff[j] + (uint32_t)(kt * 4 + part) * 1024) | dead);
             } else {
-                const bool ok = live && woff[j] != OOB && kb + 16 * part + 8 * fh < K;
-                wb[q][j][part] = load16(rw, ok ? woff[j] + (uint32_t)(kb + 16 * part) * 2 : OOB);
+                const uint32_t off = (woff[j] + (uint32_t)(kb + 16 * part) * 2) | dead;
+                wb[q][j][part] = load16(rw, kb + 16 * part + 8 * fh < K ? off : OOB);
             }
         }
     };
