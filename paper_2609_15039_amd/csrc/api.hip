@@ -8,7 +8,6 @@
 #include "splitee_probe.h"
 
 namespace splitee_host {
-size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_type);
 size_t skinny_counter_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_type);
 }
 
@@ -66,8 +65,7 @@ size_t gemm_ws_any(int64_t M, int64_t N, int64_t K, int prec)
 }
 size_t gemm_counters(int64_t M, int64_t N, int64_t K, int prec, int w_type)
 {
-    return use_skinny(M, prec) ? splitee_host::skinny_counter_bytes(M, N, K, prec, w_type)
-                               : splitee_host::gemm_counter_bytes(M, N, K, prec, w_type);
+    return use_skinny(M, prec) ? splitee_host::skinny_counter_bytes(M, N, K, prec, w_type) : 0;
 }
 
 // GEMM operand checks shared by the GEMM entry points.

@@ -96,6 +96,10 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_typ
 int launch_gemm(const void* A, int prec, int64_t lda, int64_t plane_stride, const void* W,
                 int w_type, int64_t ldw, const float* C, int64_t ldc, float* Out, int64_t ldo,
                 int64_t M, int64_t N, int64_t K, void* ws, size_t ws_bytes, hipStream_t s);
+// Binary32 GEMM, A float32, W row-major float32 or bfloat16; ws null: K is not split.
+size_t f32_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
+int launch_gemm_f32(const float* A, int64_t lda, const void* W, int w_type, int64_t ldw, const float* C, int64_t ldc,
+                    float* Out, int64_t ldo, int64_t M, int64_t N, int64_t K, void* ws, size_t ws_bytes, hipStream_t s);
 // Decode GEMM whose masked input fl32(X + eta) is formed in-kernel from X and a
 // given mask eta (both M x K float32).
 int launch_skinny_masked(const float* X, int64_t ldx, const float* eta, int64_t ld_eta, int prec,

@@ -3,20 +3,10 @@
 //   Out = A . W^T            (R, the GPU's part: r = W (x + eta))
 //   Out = fl32(A . W^T - C)  (fused unmask epilogue, Eq. add-and-then-subtract)
 //
-// A is the masked input in one of three forms: float32 (binary32 MFMA
-// v_mfma_f32_16x16x4_f32), one bfloat16 plane, or three bfloat16 planes
+// A is the masked input as one bfloat16 plane, or as three bfloat16 planes
 // hi + mid + lo that sum exactly to the float32 masked input (three bfloat16
-// MFMA passes v_mfma_f32_16x16x32_bf16 into one float32 accumulator).  W is
-// N x K row-major (nn.Linear layout), float32 or bfloat16.
-//
-// Tiling: a workgroup owns a BM x BN output tile and a contiguous range of K
-// tiles; 16-byte global loads are staged through padded LDS rows (16 bytes of
-// padding keeps the 16-byte fragment reads conflict-free), the next K tile is
-// prefetched into registers while the current one is multiplied.  When the
-// K range is split over several workgroups (split-K, to fill 256 CUs at small
-// M), each writes its float32 partial tile to the workspace and the last one to
-// arrive (device-scope counter) sums the partials in split order and applies
-// the epilogue, so results do not depend on arrival order.
+// MFMA passes into one float32 accumulator); the float32 form is gemm_f32.hip's.  W is
+// N x K bfloat16, row-major (nn.Linear layout) or in the tiled order.
 #include "gemm_dev.hpp"
 
 #include <algorithm>
@@ -52,147 +42,13 @@ __device__ __forceinline__ bool splitk_arrive(unsigned* counter, int ksplit, uns
     return *flag != 0u;
 }
 
-// The last workgroup's reduction of a BM x BN tile: the tile is walked row-major
-// in 16-byte units, CH per thread at a time; for each chunk all loads of one
-// split are issued together (agent-coherent buffer loads, sc1), then added in
-// split order, then C is subtracted and Y stored with 16-byte accesses.
-template <int BM, int BN, int NT, int CH>
-__device__ __forceinline__ void splitk_reduce(const float* tp, int ksplit, int m0, int n0, int M, int N,
-                                              const float* C, int64_t ldc, float* Out, int64_t ldo)
-{
-    constexpr int F4 = BM * BN / 4, ROW4 = BN / 4;
-    static_assert(F4 % (NT * CH) == 0, "reduction chunks");
-    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(tp), (short)0,
-                                                                       ksplit * BM * BN * 4, 0x00020000);
-    constexpr int SC1 = 16; // cache policy: coherent at agent scope
-    for (int c0 = 0; c0 < F4; c0 += NT * CH) {
-        f32x4_t sum[CH];
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-            sum[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                rp, (c0 + c * NT + (int)threadIdx.x) * 16, 0, SC1));
-        for (int q = 1; q < ksplit; ++q) {
-            f32x4_t v[CH];
-#pragma unroll
-            for (int c = 0; c < CH; ++c)
-                v[c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(
-                    rp, (q * F4 + c0 + c * NT + (int)threadIdx.x) * 16, 0, SC1));
-#pragma unroll
-            for (int c = 0; c < CH; ++c) sum[c] += v[c];
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int f = c0 + c * NT + (int)threadIdx.x;
-            const int row = m0 + f / ROW4, col = n0 + (f % ROW4) * 4;
-            if (row >= M) continue;
-            f32x4_t y = sum[c];
-            if (col + 4 <= N) {
-                if (C) y -= __builtin_bit_cast(f32x4_t, *reinterpret_cast<const float4*>(C + (int64_t)row * ldc + col));
-                *reinterpret_cast<float4*>(Out + (int64_t)row * ldo + col) = __builtin_bit_cast(float4, y);
-            } else {
-                for (int e = 0; e < 4 && col + e < N; ++e) {
-                    float v = y[e];
-                    if (C) v = v - C[(int64_t)row * ldc + col + e];
-                    Out[(int64_t)row * ldo + col + e] = v;
-                }
-            }
-        }
-    }
-}
-
 __device__ __forceinline__ void splitk_reset(unsigned* counter)
 {
     __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 constexpr int SC1 = 16;  // buffer cache policy: coherent at agent scope (write-through / bypass)
-constexpr int KSMAX = 8; // largest split-K factor of the tiled kernels
 constexpr uint32_t OOB_OFF = 0x80000000u;
-
-// Finishes the workgroup's BM x BN accumulator tile.  The tile goes through LDS
-// (row-major, rows padded by 4 floats) so that every global access below is a
-// 16-byte access of consecutive columns:
-//   ksplit == 1: Y = acc - C;
-//   ksplit  > 1: this split's partial is written (agent-coherent), the tile
-//                counter is bumped, and the last workgroup to arrive loads all
-//                partials in one round, sums them in split order, subtracts C and
-//                stores Y.
-// `lds` must hold BM * (BN + 4) + 1 floats and be free (callers sync first).
-template <int BM, int BN, int NT, int TM, int TN, int WTM, int WTN, int WGM>
-__device__ __forceinline__ void finish_tile(const f32x4_t (&acc)[TM][TN], float* lds, int m0, int n0, int M, int N,
-                                            const float* C, int64_t ldc, float* Out, int64_t ldo, int ksplit,
-                                            int split, int tile, float* part, unsigned* counters)
-{
-    constexpr int LDT = BN + 4;
-    constexpr int ROW4 = BN / 4, F4 = BM * BN / 4, PER = F4 / NT;
-    constexpr int CH = PER < 4 ? PER : 4;
-    static_assert(F4 % NT == 0 && PER % CH == 0, "epilogue split");
-    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    const int wm = wave % WGM, wn = wave / WGM;
-    const int erow = 4 * (lane / 16), ecol = lane % 16;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                lds[(wm * WTM + i * 16 + erow + r) * LDT + wn * WTN + j * 16 + ecol] = acc[i][j][r];
-    __syncthreads();
-
-    auto finish4 = [&](int f, f32x4_t y) {
-        const int row = m0 + f / ROW4, col = n0 + (f % ROW4) * 4;
-        if (row >= M) return;
-        if (col + 4 <= N) {
-            if (C) y -= __builtin_bit_cast(f32x4_t, *reinterpret_cast<const float4*>(C + (int64_t)row * ldc + col));
-            *reinterpret_cast<float4*>(Out + (int64_t)row * ldo + col) = __builtin_bit_cast(float4, y);
-        } else {
-            for (int e = 0; e < 4 && col + e < N; ++e) {
-                float v = y[e];
-                if (C) v = v - C[(int64_t)row * ldc + col + e];
-                Out[(int64_t)row * ldo + col + e] = v;
-            }
-        }
-    };
-    auto lds4 = [&](int f) {
-        return *reinterpret_cast<const f32x4_t*>(&lds[(f / ROW4) * LDT + (f % ROW4) * 4]);
-    };
-
-    if (ksplit == 1) {
-#pragma unroll
-        for (int c = 0; c < PER; ++c) finish4(tid + c * NT, lds4(tid + c * NT));
-        return;
-    }
-    const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
-        part + (int64_t)tile * ksplit * (BM * BN), (short)0, ksplit * BM * BN * 4, 0x00020000);
-#pragma unroll
-    for (int c = 0; c < PER; ++c) {
-        const int f = tid + c * NT;
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, lds4(f)), rp, (split * F4 + f) * 16, 0, SC1);
-    }
-    unsigned* flag = reinterpret_cast<unsigned*>(lds + BM * LDT);
-    if (!splitk_arrive(counters + tile, ksplit, flag)) return;
-#pragma unroll
-    for (int c0 = 0; c0 < PER; c0 += CH) {
-        f32x4_t v[KSMAX][CH];
-#pragma unroll
-        for (int q = 0; q < KSMAX; ++q)
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int f = tid + (c0 + c) * NT;
-                const uint32_t off = q < ksplit ? (uint32_t)((q * F4 + f) * 16) : OOB_OFF;
-                v[q][c] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rp, (int)off, 0, SC1));
-            }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            f32x4_t sum = v[0][c];
-#pragma unroll
-            for (int q = 1; q < KSMAX; ++q)
-                if (q < ksplit) sum += v[q][c];
-            finish4(tid + (c0 + c) * NT, sum);
-        }
-    }
-    if (tid == 0) splitk_reset(counters + tile);
-}
 
 // ----------------------------------------------- bf16 MFMA, W streamed (M > 16)
 // For weight-streaming shapes W is the only large operand and is read once: each
@@ -750,162 +606,6 @@ stream_sum_kernel(const float* __restrict__ part, int ksplit, const float* __res
             Out[(int64_t)row * ldo + col] = y;
         }
     }
-}
-
-// --------------------------------------------------------------- f32 MFMA
-// v_mfma_f32_16x16x4_f32 takes one k per lane group; four instructions cover a
-// 16-wide k slice whose elements are assigned so that each lane reads one
-// 16-byte run (k = 4 * (lane/16) + j in instruction j), identically for A and W.
-
-template <int BM, int BN, int BK, int WGM, int WGN, bool WBF16>
-__global__ void __launch_bounds__(WGM * WGN * WAVE)
-gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict__ Wv, int64_t ldw,
-                const float* __restrict__ C, int64_t ldc, float* __restrict__ Out, int64_t ldo, int M,
-                int N, int K, int mtiles, int ntiles, int ksplit, int kt_per_split,
-                float* __restrict__ part, unsigned* __restrict__ counters)
-{
-    constexpr int NT = WGM * WGN * WAVE;
-    constexpr int LDK = BK + 4;
-    constexpr int WTM = BM / WGM, WTN = BN / WGN;
-    constexpr int TM = WTM / 16, TN = WTN / 16;
-    constexpr int CPR = BK / 4;                  // 16-byte float chunks per row
-    constexpr int WCPR = WBF16 ? BK / 8 : BK / 4; // 16-byte W chunks per row
-    constexpr int ACH = BM * CPR / NT, BCH = BN * WCPR / NT;
-    static_assert(ACH * NT == BM * CPR && BCH * NT == BN * WCPR, "tile/thread mismatch");
-    static_assert(BK % 16 == 0, "k tile");
-
-    __shared__ __attribute__((aligned(16))) float sA[BM * LDK];
-    __shared__ __attribute__((aligned(16))) float sB[BN * LDK];
-
-    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
-    const int wm = wave % WGM, wn = wave / WGM;
-    const uint32_t lb = splitee::xcd_logical_block(blockIdx.x, gridDim.x);
-    const int tiles = mtiles * ntiles;
-    const int split = (int)lb / tiles, tile = (int)lb % tiles;
-    const int m0 = (tile % mtiles) * BM, n0 = (tile / mtiles) * BN;
-    const int ktiles = (K + BK - 1) / BK;
-    const int kt0 = split * kt_per_split;
-    const int kt1 = min(kt0 + kt_per_split, ktiles);
-
-    uint4 ra[ACH], rb[BCH];
-    auto gload = [&](int kt) {
-        const int kb = kt * BK;
-#pragma unroll
-        for (int c = 0; c < ACH; ++c) {
-            const int idx = tid + c * NT, row = idx / CPR, col = (idx % CPR) * 4;
-            const int gm = m0 + row, gk = kb + col;
-            ra[c] = (gm < M && gk < K) ? *reinterpret_cast<const uint4*>(A + (int64_t)gm * lda + gk)
-                                       : make_uint4(0, 0, 0, 0);
-        }
-#pragma unroll
-        for (int c = 0; c < BCH; ++c) {
-            const int idx = tid + c * NT, row = idx / WCPR, col = (idx % WCPR) * (WBF16 ? 8 : 4);
-            const int gn = n0 + row, gk = kb + col;
-            const bool ok = gn < N && gk < K;
-            if (WBF16)
-                rb[c] = ok ? *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(Wv) + (int64_t)gn * ldw + gk)
-                           : make_uint4(0, 0, 0, 0);
-            else
-                rb[c] = ok ? *reinterpret_cast<const uint4*>(reinterpret_cast<const float*>(Wv) + (int64_t)gn * ldw + gk)
-                           : make_uint4(0, 0, 0, 0);
-        }
-    };
-    auto swrite = [&]() {
-#pragma unroll
-        for (int c = 0; c < ACH; ++c) {
-            const int idx = tid + c * NT, row = idx / CPR, col = (idx % CPR) * 4;
-            *reinterpret_cast<uint4*>(&sA[row * LDK + col]) = ra[c];
-        }
-#pragma unroll
-        for (int c = 0; c < BCH; ++c) {
-            const int idx = tid + c * NT, row = idx / WCPR, col = (idx % WCPR) * (WBF16 ? 8 : 4);
-            if (WBF16) {
-                // bfloat16 -> float32 is exact: the 16 bits become the upper half
-                const uint4 v = rb[c];
-                uint4 lo = make_uint4(v.x << 16, v.x & 0xFFFF0000u, v.y << 16, v.y & 0xFFFF0000u);
-                uint4 hi = make_uint4(v.z << 16, v.z & 0xFFFF0000u, v.w << 16, v.w & 0xFFFF0000u);
-                *reinterpret_cast<uint4*>(&sB[row * LDK + col]) = lo;
-                *reinterpret_cast<uint4*>(&sB[row * LDK + col + 4]) = hi;
-            } else {
-                *reinterpret_cast<uint4*>(&sB[row * LDK + col]) = rb[c];
-            }
-        }
-    };
-
-    f32x4_t acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-    const int frow = lane % 16, fk = (lane / 16) * 4;
-    if (kt0 < kt1) gload(kt0);
-    for (int kt = kt0; kt < kt1; ++kt) {
-        __syncthreads();
-        swrite();
-        __syncthreads();
-        if (kt + 1 < kt1) gload(kt + 1);
-#pragma unroll
-        for (int ks = 0; ks < BK / 16; ++ks) {
-            float4 af[TM], bfr[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-                af[i] = *reinterpret_cast<const float4*>(&sA[(wm * WTM + i * 16 + frow) * LDK + ks * 16 + fk]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-                bfr[j] = *reinterpret_cast<const float4*>(&sB[(wn * WTN + j * 16 + frow) * LDK + ks * 16 + fk]);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].x, bfr[j].x, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].y, bfr[j].y, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].z, bfr[j].z, acc[i][j], 0, 0, 0);
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i].w, bfr[j].w, acc[i][j], 0, 0, 0);
-                }
-        }
-    }
-
-    const int erow = 4 * (lane / 16), ecol = lane % 16;
-    if (ksplit == 1) {
-        // every C load of the wave tile before the first subtraction (one wait, not one per
-        // element); elements outside M x N load C[0] and store nothing
-        float cv[TM][TN][4];
-        if (C) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int row = m0 + wm * WTM + i * 16 + erow + r, col = n0 + wn * WTN + j * 16 + ecol;
-                        cv[i][j][r] = C[row < M && col < N ? (int64_t)row * ldc + col : 0];
-                    }
-        }
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int row = m0 + wm * WTM + i * 16 + erow + r, col = n0 + wn * WTN + j * 16 + ecol;
-                    if (row < M && col < N)
-                        Out[(int64_t)row * ldo + col] = C ? acc[i][j][r] - cv[i][j][r] : acc[i][j][r];
-                }
-        return;
-    }
-    float* mypart = part + ((int64_t)tile * ksplit + split) * (BM * BN);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                store_partial(&mypart[(wm * WTM + i * 16 + erow + r) * BN + wn * WTN + j * 16 + ecol], acc[i][j][r]);
-    if (!splitk_arrive(counters + tile, ksplit, reinterpret_cast<unsigned*>(sA))) return;
-    splitk_reduce<BM, BN, WGM * WGN * WAVE, (BM * BN / 4 / (WGM * WGN * WAVE) < 8 ? BM * BN / 4 / (WGM * WGN * WAVE) : 8)>(part + (int64_t)tile * ksplit * (BM * BN), ksplit, m0, n0, M, N, C,
-                                          ldc, Out, ldo);
-    if (tid == 0) splitk_reset(counters + tile);
 }
 
 // --------------------------------------------------------- skinny (M <= 16)
@@ -1729,11 +1429,6 @@ int64_t split_cost(int64_t M, int64_t N, int64_t K, int bm, int bn, int ring, bo
     return (sp.second * bm * bn) * 16 + sp.first;
 }
 
-bool use_stream(int prec, int w_type)
-{
-    return prec != SPLITEE_PREC_F32 && (w_type == SPLITEE_BF16 || w_type == SPLITEE_BF16_TILED);
-}
-
 Plan plan_stream(int64_t M, int64_t N, int64_t K, int prec, int w_type, bool allow_split)
 {
     Plan p{};
@@ -1799,32 +1494,6 @@ double unsplit_cost(const Plan& p, int prec)
 {
     const double tile = (prec == SPLITEE_PREC_BF16X3 ? 1.05 : 0.8) * (p.bn >= 192 ? 1.0 : 0.7);
     return (double)(((int64_t)p.mtiles * p.ntiles + 255) / 256) * tile;
-}
-
-Plan plan_tiled(int64_t M, int64_t N, int64_t K, int prec, int w_type, bool allow_split)
-{
-    if (use_stream(prec, w_type)) return plan_stream(M, N, K, prec, w_type, allow_split);
-    Plan p{}; // float32 MFMA
-    p.bm = 128; p.bn = 128; p.bk = 32; p.variant = 0;
-    if (M <= 64) { p.bm = 64; p.bn = 64; p.variant = 1; }
-    (void)w_type;
-    p.mtiles = (int)((M + p.bm - 1) / p.bm);
-    p.ntiles = (int)((N + p.bn - 1) / p.bn);
-    p.ktiles = (int)((K + p.bk - 1) / p.bk);
-    int tiles = p.mtiles * p.ntiles;
-    int ks = 1;
-    if (allow_split && tiles < TARGET_WGS / 2) {
-        ks = (TARGET_WGS / 2 + tiles - 1) / tiles;
-        int max_ks = p.ktiles / 4; // keep at least 4 K tiles per split
-        if (ks > max_ks) ks = max_ks;
-        if (ks > KSMAX) ks = KSMAX;
-        if (ks < 1) ks = 1;
-    }
-    p.kt_per_split = p.ktiles > 0 ? (p.ktiles + ks - 1) / ks : 1;
-    p.ksplit = p.ktiles > 0 ? (p.ktiles + p.kt_per_split - 1) / p.kt_per_split : 1;
-    p.counter_bytes = p.ksplit > 1 ? (((size_t)tiles * 4 + 255) / 256) * 256 : 0;
-    p.part_bytes = p.ksplit > 1 ? (size_t)tiles * p.ksplit * p.bm * p.bn * 4 : 0;
-    return p;
 }
 
 // Masked-input slice bytes of one skinny workgroup holding `steps` k steps.
@@ -2008,13 +1677,7 @@ int launch_tile_weights(const uint16_t* W, int64_t ldw, int64_t N, int64_t K, ui
 
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_type)
 {
-    Plan p = plan_tiled(M, N, K, prec, w_type, true);
-    return p.counter_bytes + p.part_bytes;
-}
-
-size_t gemm_counter_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_type)
-{
-    return plan_tiled(M, N, K, prec, w_type, true).counter_bytes;
+    return prec == SPLITEE_PREC_F32 ? f32_gemm_workspace_bytes(M, N, K) : plan_stream(M, N, K, prec, w_type, true).part_bytes;
 }
 
 int launch_gemm(const void* A, int prec, int64_t lda, int64_t pstride, const void* W, int w_type,
@@ -2022,82 +1685,68 @@ int launch_gemm(const void* A, int prec, int64_t lda, int64_t pstride, const voi
                 int64_t N, int64_t K, void* ws, size_t ws_bytes, hipStream_t s)
 {
     if (M == 0 || N == 0) return SPLITEE_OK;
+    if (prec == SPLITEE_PREC_F32)
+        return launch_gemm_f32(reinterpret_cast<const float*>(A), lda, W, w_type, ldw, C, ldc, Out, ldo, M, N, K, ws,
+                               ws_bytes, s);
     const bool allow_split = ws != nullptr;
-    Plan p = plan_tiled(M, N, K, prec, w_type, allow_split);
-    if (p.ksplit > 1 && ws_bytes < p.counter_bytes + p.part_bytes) return SPLITEE_ERR_WORKSPACE;
-    unsigned* counters = p.ksplit > 1 ? reinterpret_cast<unsigned*>(ws) : nullptr;
-    float* part = p.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.counter_bytes) : nullptr;
+    Plan p = plan_stream(M, N, K, prec, w_type, allow_split);
+    if (p.ksplit > 1 && ws_bytes < p.part_bytes) return SPLITEE_ERR_WORKSPACE;
     dim3 grid((unsigned)(p.mtiles * p.ntiles * p.ksplit));
     const int m = (int)M, n = (int)N, k = (int)K;
-    if (prec == SPLITEE_PREC_F32) {
-        const float* a = reinterpret_cast<const float*>(A);
-        if (w_type == SPLITEE_BF16) {
-            if (p.variant == 0)
-                hipLaunchKernelGGL((gemm_f32_kernel<128, 128, 32, 2, 2, true>), grid, dim3(256), 0, s, a, lda, W, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, part, counters);
-            else
-                hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 32, 2, 2, true>), grid, dim3(256), 0, s, a, lda, W, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, part, counters);
-        } else {
-            if (p.variant == 0)
-                hipLaunchKernelGGL((gemm_f32_kernel<128, 128, 32, 2, 2, false>), grid, dim3(256), 0, s, a, lda, W, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, part, counters);
-            else
-                hipLaunchKernelGGL((gemm_f32_kernel<64, 64, 32, 2, 2, false>), grid, dim3(256), 0, s, a, lda, W, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, part, counters);
-        }
-    } else {
-        const uint16_t* a = reinterpret_cast<const uint16_t*>(A);
-        const uint16_t* w = reinterpret_cast<const uint16_t*>(W);
-        // the buffer loads address each operand with 31-bit byte offsets
-        const int64_t planes = prec == SPLITEE_PREC_BF16X3 ? 3 : 1;
-        const int64_t wbytes = w_type == SPLITEE_BF16_TILED ? (int64_t)splitee::tiled_weights_bytes(N, K) : N * ldw * 2;
-        if ((planes - 1) * pstride * 2 + M * lda * 2 >= (int64_t(1) << 31) || wbytes >= (int64_t(1) << 31) ||
-            p.part_bytes >= (size_t(1) << 31))
-            return SPLITEE_ERR_UNSUPPORTED;
-        if (!allow_split) { // splitee_masked_linear: no workspace
-            const SkSrc src{a, lda, pstride, nullptr, 0, nullptr, 0};
-            if (M <= GV_MMAX && w_type == SPLITEE_BF16 && M * K * 4 <= 160 * 1024)
-                return launch_gemv<false>(src, prec, W, ldw, C, ldc, Out, ldo, M, N, K, s);
-            if (M <= WSPLIT_MAX_M && plan_wsplit(M, N, prec, w_type).cost < unsplit_cost(p, prec))
-                return launch_wsplit(A, prec, lda, pstride, W, w_type, ldw, C, ldc, Out, ldo, M, N, K, s);
-        }
-        float* pp = reinterpret_cast<float*>(ws);
+    const uint16_t* a = reinterpret_cast<const uint16_t*>(A);
+    const uint16_t* w = reinterpret_cast<const uint16_t*>(W);
+    // the buffer loads address each operand with 31-bit byte offsets
+    const int64_t planes = prec == SPLITEE_PREC_BF16X3 ? 3 : 1;
+    const int64_t wbytes = w_type == SPLITEE_BF16_TILED ? (int64_t)splitee::tiled_weights_bytes(N, K) : N * ldw * 2;
+    if ((planes - 1) * pstride * 2 + M * lda * 2 >= (int64_t(1) << 31) || wbytes >= (int64_t(1) << 31) ||
+        p.part_bytes >= (size_t(1) << 31))
+        return SPLITEE_ERR_UNSUPPORTED;
+    if (!allow_split) { // splitee_masked_linear: no workspace
+        const SkSrc src{a, lda, pstride, nullptr, 0, nullptr, 0};
+        if (M <= GV_MMAX && w_type == SPLITEE_BF16 && M * K * 4 <= 160 * 1024)
+            return launch_gemv<false>(src, prec, W, ldw, C, ldc, Out, ldo, M, N, K, s);
+        if (M <= WSPLIT_MAX_M && plan_wsplit(M, N, prec, w_type).cost < unsplit_cost(p, prec))
+            return launch_wsplit(A, prec, lda, pstride, W, w_type, ldw, C, ldc, Out, ldo, M, N, K, s);
+    }
+    float* pp = reinterpret_cast<float*>(ws);
 #define ST_LAUNCH(NP, BM_, BN_, WGM_, D_, NW_, T_) hipLaunchKernelGGL((gemm_stream_kernel<NP, BM_, BN_, WGM_, D_, NW_, T_>), grid, dim3(NW_ * WAVE), 0, s, a, lda, pstride, w, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, pp)
 #define ST_SUM(BM_, BN_, WGM_, WGN_) hipLaunchKernelGGL((stream_sum_kernel<BM_, BN_, WGM_, WGN_>), g2, dim3(256), 0, s, pp, p.ksplit, C, ldc, Out, ldo, m, n, p.mtiles, tiles)
+    switch (p.variant) {
+    case 10: ST_LAUNCH(3, 128, 256, 1, 2, 4, false); break;
+    case 11: ST_LAUNCH(3, 64, 256, 1, 3, 4, false); break;
+    case 12: ST_LAUNCH(1, 128, 256, 1, 2, 4, false); break;
+    case 13: ST_LAUNCH(1, 64, 256, 1, 3, 4, false); break;
+    case 14: ST_LAUNCH(3, 128, 128, 2, 2, 4, false); break;
+    case 15: ST_LAUNCH(1, 128, 128, 2, 2, 4, false); break;
+    case 22: ST_LAUNCH(3, 128, 256, 2, 2, 8, true); break;
+    case 23: ST_LAUNCH(1, 128, 256, 2, 2, 8, true); break;
+    case 24: ST_LAUNCH(3, 64, 256, 1, 2, 8, true); break;
+    case 25: ST_LAUNCH(1, 64, 256, 1, 2, 8, true); break;
+    case 26: ST_LAUNCH(3, 64, 128, 2, 3, 8, true); break;
+    case 28: ST_LAUNCH(3, 128, 192, 4, 2, 8, true); break;
+    case 29: ST_LAUNCH(1, 128, 192, 4, 2, 8, true); break;
+    case 30: ST_LAUNCH(3, 64, 256, 1, 2, 4, true); break;
+    case 31: ST_LAUNCH(3, 64, 192, 2, 2, 4, true); break;
+    default: ST_LAUNCH(1, 64, 128, 2, 3, 8, true); break;
+    }
+    if (p.ksplit > 1) {
+        const int tiles = p.mtiles * p.ntiles;
+        const int64_t units = (int64_t)tiles * p.bm * p.bn / 4; // float4 units of the partial tiles
+        const dim3 g2((unsigned)((units + 255) / 256));
         switch (p.variant) {
-        case 10: ST_LAUNCH(3, 128, 256, 1, 2, 4, false); break;
-        case 11: ST_LAUNCH(3, 64, 256, 1, 3, 4, false); break;
-        case 12: ST_LAUNCH(1, 128, 256, 1, 2, 4, false); break;
-        case 13: ST_LAUNCH(1, 64, 256, 1, 3, 4, false); break;
-        case 14: ST_LAUNCH(3, 128, 128, 2, 2, 4, false); break;
-        case 15: ST_LAUNCH(1, 128, 128, 2, 2, 4, false); break;
-        case 22: ST_LAUNCH(3, 128, 256, 2, 2, 8, true); break;
-        case 23: ST_LAUNCH(1, 128, 256, 2, 2, 8, true); break;
-        case 24: ST_LAUNCH(3, 64, 256, 1, 2, 8, true); break;
-        case 25: ST_LAUNCH(1, 64, 256, 1, 2, 8, true); break;
-        case 26: ST_LAUNCH(3, 64, 128, 2, 3, 8, true); break;
-        case 28: ST_LAUNCH(3, 128, 192, 4, 2, 8, true); break;
-        case 29: ST_LAUNCH(1, 128, 192, 4, 2, 8, true); break;
-        case 30: ST_LAUNCH(3, 64, 256, 1, 2, 4, true); break;
-        case 31: ST_LAUNCH(3, 64, 192, 2, 2, 4, true); break;
-        default: ST_LAUNCH(1, 64, 128, 2, 3, 8, true); break;
+        case 10: case 12: ST_SUM(128, 256, 1, 4); break;
+        case 11: case 13: ST_SUM(64, 256, 1, 4); break;
+        case 14: case 15: ST_SUM(128, 128, 2, 2); break;
+        case 22: case 23: ST_SUM(128, 256, 2, 4); break;
+        case 24: case 25: ST_SUM(64, 256, 1, 8); break;
+        case 28: case 29: ST_SUM(128, 192, 4, 2); break;
+        case 30: ST_SUM(64, 256, 1, 4); break;
+        case 31: ST_SUM(64, 192, 2, 2); break;
+        default: ST_SUM(64, 128, 2, 4); break;
         }
-        if (p.ksplit > 1) {
-            const int tiles = p.mtiles * p.ntiles;
-            const int64_t units = (int64_t)tiles * p.bm * p.bn / 4; // float4 units of the partial tiles
-            const dim3 g2((unsigned)((units + 255) / 256));
-            switch (p.variant) {
-            case 10: case 12: ST_SUM(128, 256, 1, 4); break;
-            case 11: case 13: ST_SUM(64, 256, 1, 4); break;
-            case 14: case 15: ST_SUM(128, 128, 2, 2); break;
-            case 22: case 23: ST_SUM(128, 256, 2, 4); break;
-            case 24: case 25: ST_SUM(64, 256, 1, 8); break;
-            case 28: case 29: ST_SUM(128, 192, 4, 2); break;
-            case 30: ST_SUM(64, 256, 1, 4); break;
-            case 31: ST_SUM(64, 192, 2, 2); break;
-            default: ST_SUM(64, 128, 2, 4); break;
-            }
-        }
+    }
 #undef ST_SUM
 #undef ST_LAUNCH
-    }
     return hipGetLastError() == hipSuccess ? SPLITEE_OK : SPLITEE_ERR_HIP;
 }
 
@@ -2218,9 +1867,9 @@ int launch_gemm_masked(const float* X, int64_t ldx, const float* eta, int64_t ld
         (int64_t)splitee::tiled_weights_bytes(N, K) >= (int64_t(1) << 31))
         return SPLITEE_ERR_UNSUPPORTED;
     const bool allow_split = ws != nullptr;
-    Plan p = plan_tiled(M, N, K, prec, w_type, allow_split);
+    Plan p = plan_stream(M, N, K, prec, w_type, allow_split);
     if (p.variant != 24 && p.variant != 25 && p.variant != 26 && p.variant != 27) return SPLITEE_ERR_UNSUPPORTED;
-    if (p.ksplit > 1 && ws_bytes < p.counter_bytes + p.part_bytes) return SPLITEE_ERR_WORKSPACE;
+    if (p.ksplit > 1 && ws_bytes < p.part_bytes) return SPLITEE_ERR_WORKSPACE;
     if (p.part_bytes >= (size_t(1) << 31)) return SPLITEE_ERR_UNSUPPORTED; // the sum kernel's buffer offsets
     float* pp = reinterpret_cast<float*>(ws);
     const uint16_t* w = reinterpret_cast<const uint16_t*>(W);
