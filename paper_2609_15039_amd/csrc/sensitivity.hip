@@ -2,7 +2,8 @@
 // power method on W^T W, and the vector norms ||alpha||_4, ||beta||_2 that the
 // sensitivity bounds of Theorems 1-3 take.
 //
-// One round of the power method (v unit, u = W v, sigma = ||u||, z = W^T u,
+// Where W fits the chip's registers, one kernel runs every round (below: W resident in registers).
+// Otherwise one round of the power method (v unit, u = W v, sigma = ||u||, z = W^T u,
 // v <- z / ||z||) reads W from HBM once.  A workgroup takes a tile of RB rows x K
 // into registers (thread t holds columns 8 t + 2048 c .. + 7 of every row), forms
 // the RB dot products with v (per-thread partials, then one cross-lane reduction
@@ -374,14 +375,345 @@ __global__ void __launch_bounds__(PI_NT) vec_norms_kernel(const float* __restric
     }
 }
 
+// ------------------------------------------------ W resident in registers
+// Where the whole matrix fits the register files of one 1024-thread workgroup per CU, every
+// round runs in one kernel: workgroup b keeps rows b RB .. + RB - 1 (thread t the columns 4 t +
+// 4096 c .. + 3 of each), so W is read once for all rounds, and a round is left with its
+// arithmetic and two exchanges through memory: the partial rows of z = W^T u, each column block
+// summed by one workgroup, and z itself.  What bounds it is then the latency of the exchanges
+// and the wave reductions, so
+//  - a workgroup writes its partial row, waits for the stores, writes its flag (the round's number)
+//    and polls all flags at once, one per thread, each in a 256-byte line of its own (side by side they
+//    lie in a few memory channels, and the polls of 256 workgroups took 5 us instead of 2);
+//  - z needs no flag: its buffer holds PX_EMPTY until the sums are written, and every thread polls its
+//    own columns (two buffers in turn; a workgroup empties its block of the one just used);
+//  - the dot products are summed over the wave by lane swaps and rotations in registers (through LDS they
+//    took 5 us of a round).
+// The launch is cooperative (every workgroup resident); a poll gives up after PI_SPINS tries all the same,
+// and the host then runs the rounds with W streamed.
+//
+// Parts, flags and z are read and written with agent scope (sc1: written through and read past the
+// XCDs' caches).  A partial row is rewritten after its workgroup read the next z, which exists
+// only after every workgroup read its parts.  A block of z is emptied when every flag says that
+// the round's z was read, and filled again a round later, behind the flags of that round.
+//
+// Llama-3.2-3B W_up (8192 x 3072 bfloat16): 20.8 -> 13.0 us a round; a 969 x 1160 matrix 13.1 -> 10.2.
+constexpr int PX_NT = 1024;
+constexpr int PX_NW = PX_NT / WAVE;
+constexpr int PX_CW = 4 * PX_NT;          // columns of one register chunk
+constexpr int PX_MAX_WGS = 256;
+constexpr int PX_FLAG = 64;               // words from flag to flag
+constexpr int PX_AGENT = 16;              // buffer cache policy: agent scope
+constexpr unsigned PX_EMPTY = 0xFFFFFFFFu; // a NaN that z never holds
+constexpr unsigned PI_SPINS = 1u << 22;
+
+struct PxArgs {
+    const void* W; int64_t ldw; int N, K, iters;
+    float* z[2]; float* zpart; double* upart; double* sig;
+    unsigned* flags; // PX_MAX_WGS flags, then the error word
+};
+
+template <bool WBF16> struct W4;
+template <> struct W4<true> {
+    uint2 q;
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff)
+    {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, 0, 0);
+        q = make_uint2(v.x, v.y);
+    }
+    __device__ __forceinline__ void fence() { asm volatile("" : "+v"(q.x), "+v"(q.y)); }
+    __device__ __forceinline__ void get(float (&w)[4]) const
+    {
+        w[0] = __uint_as_float(q.x << 16); w[1] = __uint_as_float(q.x & 0xFFFF0000u);
+        w[2] = __uint_as_float(q.y << 16); w[3] = __uint_as_float(q.y & 0xFFFF0000u);
+    }
+};
+template <> struct W4<false> {
+    u32x4 q;
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff)
+    {
+        q = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0);
+    }
+    __device__ __forceinline__ void fence() {}
+    __device__ __forceinline__ void get(float (&w)[4]) const
+    {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = __uint_as_float(q[e]);
+    }
+};
+
+// Four values per lane summed over the wave in registers: lanes 16 r .. + 15 end with the sum of
+// v[r].  Two halving exchanges by lane swaps, then rotations within 16 lanes (a fixed tree).
+__device__ __forceinline__ float px_rows_sum(const float (&v)[4])
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    float h[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) { // {v[i] low, v[i + 2] low} + {v[i] high, v[i + 2] high}
+        const u32x2 t = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[i + 2]), false, false);
+        h[i] = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    }
+    const u32x2 t = __builtin_amdgcn_permlane16_swap(__float_as_uint(h[0]), __float_as_uint(h[1]), false, false);
+    float s = __uint_as_float(t[0]) + __uint_as_float(t[1]);
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x128, 0xF, 0xF, false)); // row_ror:8
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x124, 0xF, 0xF, false)); // row_ror:4
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x122, 0xF, 0xF, false)); // row_ror:2
+    s += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(s), 0x121, 0xF, 0xF, false)); // row_ror:1
+    return s;
+}
+
+// The sum over the wave, in every lane: halves, quarters, then rotations within 16 lanes.
+__device__ __forceinline__ double px_wave_sum(double v)
+{
+    typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+    auto add = [&](u32x2 lo, u32x2 hi) {
+        return __builtin_bit_cast(double, u32x2{lo[0], hi[0]}) + __builtin_bit_cast(double, u32x2{lo[1], hi[1]});
+    };
+    u32x2 w = __builtin_bit_cast(u32x2, v);
+    v = add(__builtin_amdgcn_permlane32_swap(w[0], w[0], false, false), __builtin_amdgcn_permlane32_swap(w[1], w[1], false, false));
+    w = __builtin_bit_cast(u32x2, v);
+    v = add(__builtin_amdgcn_permlane16_swap(w[0], w[0], false, false), __builtin_amdgcn_permlane16_swap(w[1], w[1], false, false));
+#define PX_ROR(n)                                                                                              \
+    w = __builtin_bit_cast(u32x2, v);                                                                          \
+    v += __builtin_bit_cast(double, u32x2{(unsigned)__builtin_amdgcn_update_dpp(0, (int)w[0], 0x120 + n, 0xF, 0xF, false), \
+                                          (unsigned)__builtin_amdgcn_update_dpp(0, (int)w[1], 0x120 + n, 0xF, 0xF, false)})
+    PX_ROR(8);
+    PX_ROR(4);
+    PX_ROR(2);
+    PX_ROR(1);
+#undef PX_ROR
+    return v;
+}
+
+// Every workgroup's flag has reached `round`; false (in all threads) after PI_SPINS tries.
+__device__ __forceinline__ bool px_wait(unsigned* flags, int G, unsigned round, unsigned* err)
+{
+    bool ok = true;
+    if ((int)threadIdx.x < G) {
+        unsigned n = 0;
+        while (__hip_atomic_load(flags + threadIdx.x * PX_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < round)
+            if (++n == PI_SPINS) {
+                ok = false;
+                __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+    }
+    return __syncthreads_and(ok) != 0;
+}
+
+// This workgroup's stores are complete; then its flag.
+__device__ __forceinline__ void px_signal(unsigned* flag, unsigned round)
+{
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int CH, int RB, bool WBF16>
+__global__ void __launch_bounds__(PX_NT) pi_resident_kernel(PxArgs a)
+{
+    constexpr int ES = WBF16 ? 2 : 4;
+    static_assert(RB <= WAVE && RB % 4 == 0, "rows");
+    __shared__ float red[PX_NW][RB];
+    __shared__ double red_zz[PX_NW];
+    __shared__ float u_s[RB];
+    extern __shared__ __attribute__((aligned(16))) float4 cols[]; // G x q4 float4
+    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
+    const int b = blockIdx.x, G = gridDim.x, n0 = b * RB, K = a.K;
+    unsigned *flags = a.flags, *err = a.flags + PX_MAX_WGS * PX_FLAG;
+
+    // the workgroup's rows of W (zeros past N and K)
+    W4<WBF16> w[RB][CH];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<char*>(reinterpret_cast<const char*>(a.W) + (int64_t)(n0 + r < a.N ? n0 + r : 0) * a.ldw * ES), (short)0,
+            n0 + r < a.N ? K * ES : 0, 0x00020000);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const int k = 4 * tid + PX_CW * c;
+            w[r][c].load(rs, k < K ? (uint32_t)(k * ES) : PI_OOB);
+        }
+    }
+    const __amdgpu_buffer_rsrc_t rp =
+        __builtin_amdgcn_make_buffer_rsrc(a.zpart, (short)0, (int)((int64_t)G * K * 4), 0x00020000);
+    const int k4 = K / 4, q4 = (k4 + G - 1) / G;  // float4 columns of z, and of this workgroup's block of it
+    const int qn = max(0, min(q4, k4 - b * q4));
+
+    for (int it = 0; it < a.iters; ++it) {
+        const unsigned round = (unsigned)it + 1u;
+        const __amdgpu_buffer_rsrc_t rz = __builtin_amdgcn_make_buffer_rsrc(a.z[it & 1], (short)0, K * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rn = __builtin_amdgcn_make_buffer_rsrc(a.z[(it & 1) ^ 1], (short)0, K * 4, 0x00020000);
+        float x[CH][4], zacc[CH][4];
+        double zz = 0.0;
+        bool ok = true;
+        for (unsigned n = 0;; ++n) { // this thread's columns of z, once they are all there (zeros past K)
+            bool full = true;
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int k = 4 * tid + PX_CW * c;
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rz, (int)(k < K ? (uint32_t)k * 4 : PI_OOB), 0, PX_AGENT);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    x[c][e] = __uint_as_float(v[e]);
+                    full = full && v[e] != PX_EMPTY;
+                }
+            }
+            if (full) break;
+            if (n == PI_SPINS) {
+                ok = false;
+                __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                zacc[c][e] = 0.f;
+                zz += (double)x[c][e] * (double)x[c][e];
+            }
+        // W z: four rows at a time
+#pragma unroll
+        for (int g = 0; g < RB / 4; ++g) {
+            float acc[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                acc[r] = 0.f;
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    float f[4];
+                    w[4 * g + r][c].get(f);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[r] = fmaf(f[e], x[c][e], acc[r]);
+                }
+            }
+            const float s = px_rows_sum(acc);
+            if (lane % 16 == 0) red[wave][4 * g + lane / 16] = s;
+        }
+        zz = px_wave_sum(zz);
+        if (lane == 0) red_zz[wave] = zz;
+#pragma unroll
+        for (int r = 0; r < RB; ++r)
+#pragma unroll
+            for (int c = 0; c < CH; ++c) w[r][c].fence();
+        if (!__syncthreads_and(ok)) return;
+        if (wave == 0) { // u = W z / ||z||: the waves' sums in a fixed tree, lane = row
+            double n2 = 0.0;
+#pragma unroll
+            for (int v = 0; v < PX_NW; ++v) n2 += red_zz[v];
+            const float inv = n2 > 0.0 ? (float)(1.0 / sqrt(n2)) : 0.f;
+            float t[PX_NW];
+#pragma unroll
+            for (int v = 0; v < PX_NW; ++v) t[v] = lane < RB ? red[v][lane] : 0.f;
+#pragma unroll
+            for (int d = PX_NW / 2; d >= 1; d /= 2)
+#pragma unroll
+                for (int v = 0; v < d; ++v) t[v] += t[v + d];
+            const float u = t[0] * inv; // rows past N are zeros
+            if (lane < RB) u_s[lane] = u;
+            const double uu = px_wave_sum(lane < RB ? (double)u * (double)u : 0.0);
+            if (lane == 0) __hip_atomic_store(a.upart + b, uu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __syncthreads();
+        const bool last = it + 1 == a.iters; // its z is not needed
+        if (!last) {
+#pragma unroll
+            for (int r = 0; r < RB; ++r) {
+                const float ur = u_s[r];
+#pragma unroll
+                for (int c = 0; c < CH; ++c) {
+                    float f[4];
+                    w[r][c].get(f);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) zacc[c][e] = fmaf(f[e], ur, zacc[c][e]);
+                }
+            }
+#pragma unroll
+            for (int r = 0; r < RB; ++r)
+#pragma unroll
+                for (int c = 0; c < CH; ++c) w[r][c].fence();
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                const int k = 4 * tid + PX_CW * c;
+                const u32x4 v = {__float_as_uint(zacc[c][0]), __float_as_uint(zacc[c][1]), __float_as_uint(zacc[c][2]),
+                                 __float_as_uint(zacc[c][3])};
+                __builtin_amdgcn_raw_buffer_store_b128(v, rp, (int)(k < K ? ((uint32_t)b * (uint32_t)K + (uint32_t)k) * 4u : PI_OOB), 0,
+                                                       PX_AGENT);
+            }
+        }
+        px_signal(flags + b * PX_FLAG, round);
+        if (!px_wait(flags, G, round, err)) return;
+        if (b == 0 && wave == PX_NW - 1) { // sigma = ||u||
+            double s = 0.0;
+            for (int i = lane; i < G; i += WAVE) s += __hip_atomic_load(a.upart + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            s = wave_sum(s);
+            if (lane == 0) a.sig[it] = sqrt(s);
+        }
+        if (last) break;
+        // z: this workgroup's block of columns, the G partial rows in a fixed tree
+        for (int i = tid; i < G * q4; i += PX_NT) {
+            const int p = i / q4, q = i - p * q4;
+            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(
+                rp, (int)(q < qn ? ((uint32_t)p * (uint32_t)K + (uint32_t)(b * q4 + q) * 4u) * 4u : PI_OOB), 0, PX_AGENT);
+            cols[i] = __builtin_bit_cast(float4, v);
+        }
+        __syncthreads();
+        for (int q = wave; q < qn; q += PX_NW) {
+            float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int p = lane; p < G; p += WAVE) {
+                const float4 v = cols[p * q4 + q];
+                s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+            }
+#pragma unroll
+            for (int d = 32; d >= 1; d >>= 1) {
+                s.x += __shfl_xor(s.x, d, WAVE);
+                s.y += __shfl_xor(s.y, d, WAVE);
+                s.z += __shfl_xor(s.z, d, WAVE);
+                s.w += __shfl_xor(s.w, d, WAVE);
+            }
+            if (lane == 0) {
+                u32x4 v = __builtin_bit_cast(u32x4, s);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = v[e] == PX_EMPTY ? 0x7FC00000u : v[e];
+                __builtin_amdgcn_raw_buffer_store_b128(v, rn, (b * q4 + q) * 16, 0, PX_AGENT);
+                __builtin_amdgcn_raw_buffer_store_b128(u32x4{PX_EMPTY, PX_EMPTY, PX_EMPTY, PX_EMPTY}, rz, (b * q4 + q) * 16, 0, PX_AGENT);
+            }
+        }
+    }
+}
+
+__global__ void __launch_bounds__(PI_NT) px_clear_kernel(unsigned* __restrict__ flags, int n, unsigned* __restrict__ z, int K)
+{
+    for (int i = blockIdx.x * PI_NT + threadIdx.x; i < K; i += gridDim.x * PI_NT) z[i] = PX_EMPTY;
+    for (int i = blockIdx.x * PI_NT + threadIdx.x; i < n; i += gridDim.x * PI_NT) flags[i] = 0u;
+}
+
+// Rows per workgroup of the resident kernel: the fewest instantiated ones that cover N with at
+// most 256 workgroups; 0 where the registers do not hold the matrix.
+int px_rows(int64_t N, int64_t K, bool bf16)
+{
+    static const int R1[] = {4, 8, 16, 24, 32, 40, 0}, R2[] = {4, 8, 12, 16, 20, 0}, R3[] = {4, 8, 12, 0}, R4[] = {4, 8, 0};
+    static const int F1[] = {4, 8, 16, 20, 0}, F2[] = {4, 8, 0}, F3[] = {4, 0};
+    const int64_t ch = (K + PX_CW - 1) / PX_CW;
+    const int* l = bf16 ? (ch == 1 ? R1 : ch == 2 ? R2 : ch == 3 ? R3 : R4) : (ch == 1 ? F1 : ch == 2 ? F2 : F3);
+    if (ch < 1 || ch > 4) return 0;
+    for (; *l; ++l)
+        if ((N + *l - 1) / *l <= PX_MAX_WGS) return *l;
+    return 0;
+}
+
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
 struct PiLayout {
     double* sig;     // iters
     double* upart;   // nwg
     double* zn_part; // nzn
-    float* z;        // K
+    float* z;        // K, and the resident kernel's second one at zstride
+    int64_t zstride;
     float* zpart;    // nwg x K
+    unsigned* flags; // of the resident kernel
     size_t bytes;
 };
 
@@ -401,7 +733,8 @@ int64_t pi_workgroups(int64_t N, int64_t K, bool bf16)
 
 PiLayout pi_layout(void* ws, int64_t N, int64_t K, int iters, bool bf16)
 {
-    const int64_t nwg = pi_workgroups(N, K, bf16), nzn = (K + PR_CB - 1) / PR_CB;
+    const int rb = px_rows(N, K, bf16);
+    const int64_t nwg = std::max(pi_workgroups(N, K, bf16), rb ? (N + rb - 1) / rb : 0), nzn = (K + PR_CB - 1) / PR_CB;
     const uintptr_t base = reinterpret_cast<uintptr_t>(ws);
     PiLayout L{};
     size_t off = 0;
@@ -412,9 +745,12 @@ PiLayout pi_layout(void* ws, int64_t N, int64_t K, int iters, bool bf16)
     L.zn_part = reinterpret_cast<double*>(base + off);
     off += align256((size_t)nzn * 8);
     L.z = reinterpret_cast<float*>(base + off);
-    off += align256((size_t)K * 4);
+    L.zstride = (int64_t)(align256((size_t)K * 4) / 4);
+    off += 2 * align256((size_t)K * 4);
     L.zpart = reinterpret_cast<float*>(base + off);
     off += align256((size_t)nwg * K * 4);
+    L.flags = reinterpret_cast<unsigned*>(base + off);
+    off += align256((size_t)(PX_MAX_WGS * PX_FLAG + 1) * 4);
     L.bytes = off;
     return L;
 }
@@ -431,6 +767,37 @@ void launch_round(const void* W, bool bf16, int64_t ldw, int N, int K, const PiL
                            (const float*)L.z, (const double*)L.zn_part, nzn, L.upart, L.zpart);
 }
 
+// All rounds in one cooperative launch; false if the device cannot hold it (nothing was enqueued).
+template <int CH, int RB, bool WBF16>
+bool launch_resident(const PxArgs& a, int G, hipStream_t s)
+{
+    const int q4 = (a.K / 4 + G - 1) / G;
+    PxArgs args = a;
+    void* kp[] = {&args};
+    if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&pi_resident_kernel<CH, RB, WBF16>), dim3((unsigned)G), dim3(PX_NT), kp,
+                                   (unsigned)((size_t)G * q4 * 16), s) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    return false;
+}
+
+bool run_resident(const PxArgs& a, int rb, bool bf16, hipStream_t s)
+{
+    const int ch = (a.K + PX_CW - 1) / PX_CW, G = (a.N + rb - 1) / rb;
+#define PX(CH, RB) case CH * 100 + RB: return bf16 ? launch_resident<CH, RB, true>(a, G, s) : false
+#define PXF(CH, RB) case CH * 100 + RB: return bf16 ? launch_resident<CH, RB, true>(a, G, s) : launch_resident<CH, RB, false>(a, G, s)
+    switch (ch * 100 + rb) {
+    PXF(1, 4); PXF(1, 8); PXF(1, 16); PX(1, 24); PX(1, 32); PX(1, 40);
+    case 120: return launch_resident<1, 20, false>(a, G, s);
+    PXF(2, 4); PXF(2, 8); PX(2, 12); PX(2, 16); PX(2, 20);
+    PXF(3, 4); PX(3, 8); PX(3, 12);
+    PXF(4, 4); PX(4, 8);
+    default: return false;
+    }
+#undef PX
+#undef PXF
+}
+
 }  // namespace
 
 namespace splitee_host {
@@ -443,10 +810,11 @@ size_t spectral_workspace_bytes(int64_t N, int64_t K, int iters)
     return std::max(pi_layout(nullptr, N, K, iters, true).bytes, pi_layout(nullptr, N, K, iters, false).bytes);
 }
 
-int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int64_t K, int iters, uint64_t seed,
-                         uint64_t sid, double* sigma, double* history, void* ws, hipStream_t s)
+// The rounds and their results on the host, W resident (rb rows per workgroup) or streamed (rb 0).
+// *gave_up: the resident kernel's workgroups did not run together.
+static int power_rounds(const void* W, bool bf16, int64_t ldw, int64_t N, int64_t K, int iters, uint64_t seed,
+                        uint64_t sid, double* sigma, double* history, void* ws, int rb, bool* gave_up, hipStream_t s)
 {
-    const bool bf16 = w_type == SPLITEE_BF16;
     const PiLayout L = pi_layout(ws, N, K, iters, bf16);
     const int nwg = (int)pi_workgroups(N, K, bf16), nzn = (int)((K + PR_CB - 1) / PR_CB);
     const int ch = pi_chunks(K);
@@ -456,7 +824,14 @@ int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int6
     if (rc != SPLITEE_OK) return rc;
     hipLaunchKernelGGL(pi_reduce_kernel, dim3(nzn), dim3(PI_NT), 0, s, (const float*)L.zpart, 1, (int)K, L.z,
                        L.zn_part, (const double*)nullptr, 0, (double*)nullptr);
-    for (int it = 0; it < iters; ++it) {
+    bool resident = false;
+    unsigned px_err = 0;
+    if (rb) {
+        hipLaunchKernelGGL(px_clear_kernel, dim3(64), dim3(PI_NT), 0, s, L.flags, PX_MAX_WGS * PX_FLAG + 1,
+                           reinterpret_cast<unsigned*>(L.z + L.zstride), (int)K);
+        resident = run_resident(PxArgs{W, ldw, (int)N, (int)K, iters, {L.z, L.z + L.zstride}, L.zpart, L.upart, L.sig, L.flags}, rb, bf16, s);
+    }
+    for (int it = 0; it < iters && !resident; ++it) {
         switch (ch) {
         case 1: launch_round<1>(W, bf16, ldw, (int)N, (int)K, L, nwg, nzn, s); break;
         case 2: launch_round<2>(W, bf16, ldw, (int)N, (int)K, L, nwg, nzn, s); break;
@@ -477,8 +852,24 @@ int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int6
     if (history &&
         hipMemcpyAsync(history, L.sig, (size_t)iters * sizeof(double), hipMemcpyDeviceToHost, s) != hipSuccess)
         return SPLITEE_ERR_HIP;
-    return hipStreamSynchronize(s) == hipSuccess ? SPLITEE_OK : SPLITEE_ERR_HIP;
+    if (resident && hipMemcpyAsync(&px_err, L.flags + PX_MAX_WGS * PX_FLAG, sizeof(px_err), hipMemcpyDeviceToHost, s) != hipSuccess)
+        return SPLITEE_ERR_HIP;
+    if (hipStreamSynchronize(s) != hipSuccess) return SPLITEE_ERR_HIP;
+    *gave_up = px_err != 0;
+    return SPLITEE_OK;
 }
+
+int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int64_t K, int iters, uint64_t seed,
+                         uint64_t sid, double* sigma, double* history, void* ws, hipStream_t s)
+{
+    const bool bf16 = w_type == SPLITEE_BF16;
+    bool gave_up = false;
+    int rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, px_rows(N, K, bf16), &gave_up, s);
+    if (rc == SPLITEE_OK && gave_up)
+        rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, 0, &gave_up, s);
+    return rc;
+}
+
 
 int launch_vec_norms(const float* alpha, const float* beta, int64_t d, double* out_dev, double* out_host,
                      hipStream_t s)
