@@ -141,7 +141,9 @@ def _ptr(t):
 
 def _stream(stream):
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the handle alone: torch.cuda.current_stream() builds a Stream object around it, 2.8 us a
+        # call against 0.3 (of 12.5 us of host time of a small fused call)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return stream

@@ -358,7 +358,8 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, bool allow_split)
     const size_t off = ((size_t)((N + 31) / 32) * 4 + 255) / 256 * 256;
     F32Plan best{};
     double best_cost = -1.0;
-    for (int tm = 1; tm <= F_MAX_TM; ++tm)
+    // (rows that one more 16-row block would only pad are not tried: the planning costs host time)
+    for (int tm = 1; tm <= F_MAX_TM && 16 * (tm - 1) < M; ++tm)
         for (int tn = 1; tn <= f32_max_tn(tm); ++tn) {
             const int64_t mtiles = (M + 16 * tm - 1) / (16 * tm), tiles = mtiles * ((N + 64 * tn - 1) / (64 * tn));
             const int64_t full = tiles / 256 * 256, rem = tiles - full;

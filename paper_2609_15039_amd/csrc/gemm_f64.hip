@@ -320,7 +320,7 @@ F64Plan plan_f64(int64_t M, int64_t N, int64_t K)
     const int ktiles = (int)((K + D_BK - 1) / D_BK);
     F64Plan best{};
     double best_cost = -1.0;
-    for (int tm = 1; tm <= D_MAX_TM; ++tm) {
+    for (int tm = 1; tm <= D_MAX_TM && 16 * (tm - 1) < M; ++tm) {
         const int64_t mtiles = (M + 16 * tm - 1) / (16 * tm), tiles = mtiles * ((N + D_BN - 1) / D_BN);
         const int64_t full = tiles / 256 * 256, rem = tiles - full;
         const double ktile = 0.24 * tm + 0.06;
