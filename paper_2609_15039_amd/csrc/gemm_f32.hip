@@ -11,9 +11,11 @@
 //    by two reads less LDS and measured the same);
 //  - one barrier per K tile, in the middle of its MFMAs: the fragments of the next half tile are
 //    read under the MFMAs of this one.
-// The matrix cores are then busy 83% of the cycles, at 2.2 GHz.  An accumulator chain runs over 192 k
+// The matrix cores are then busy 83% of the cycles, at 2.2 GHz.  An accumulator chain runs over 96 or 128 k
 // and is then added into a second set of registers, so the rounding error no longer grows with
-// K: 2.6e-7 of the result at K = 9728 where one chain has 1.7e-6, and 8e-7 before (five splits).
+// K: 2.0e-7 to 2.5e-7 of the result at K = 9728 where one chain has 1.7e-6, and 8e-7 before (five splits).
+// Chains of 192 k lost to the former splits at K = 256-1024 (2.5e-7 against 2.1e-7, now 2.1e-7) and are
+// as fast within 1% on most shapes.
 //
 // bfloat16 W, Qwen3-4B: 333 tokens QKV 181 -> 92 us, O 124 -> 68, gate/up 357 -> 277 (120 TFLOP/s), Down
 // 268 -> 149; 1024 tokens Down 635 -> 389 (131 TFLOP/s); one token O 30.6 -> 10.6; 32 x 512 x 512 8.4 -> 6.1;
@@ -28,7 +30,7 @@ namespace {
 constexpr int F_NW = 4;           // waves of a workgroup, side by side along N
 constexpr int F_NT = F_NW * WAVE;
 constexpr int F_BK = 32;          // k of one stage: 128 bytes of an A row
-constexpr int F_CHAIN = 6;        // K tiles that one accumulator chain runs over
+constexpr int F_CHAIN = 4;        // K tiles that one accumulator chain runs over at most
 constexpr int F_MAX_TM = 8;       // 16-row blocks of a tile
 constexpr int f32_max_tn(int tm) { return tm >= 4 && tm < 8 ? 2 : 1; } // 64-column blocks (128 x 128 would spill)
 
@@ -46,12 +48,12 @@ __device__ __forceinline__ unsigned char* f32_stage()
 // Rows of the A stage: a tile's rows rounded up so that every wave loads as many.
 constexpr int f32_stage_rows(int tm) { return (16 * tm + 31) / 32 * 32; }
 constexpr int f32_stage_bytes(int tm, int tn, bool wbf16) { return f32_stage_rows(tm) * 128 + 64 * tn * (wbf16 ? 64 : 128); }
-// Stages: as many as let two workgroups share a CU's 160 KB, 2 to 6 (one wave per SIMD reaches
-// 141 TFLOP/s, two 154).
+// Stages: as many as let two workgroups share a CU's 160 KB (one wave per SIMD reaches 141 TFLOP/s, two
+// 154), 2, 3, 4 or 6: numbers that chains of at most F_CHAIN K tiles fit.
 constexpr int f32_stages(int tm, int tn, bool wbf16)
 {
     const int s = 78 * 1024 / f32_stage_bytes(tm, tn, wbf16);
-    return s < 2 ? 2 : s > 6 ? 6 : s;
+    return s < 2 ? 2 : s >= 6 ? 6 : s == 5 ? 4 : s;
 }
 
 template <int TM, int TN, bool WBF16>
@@ -123,7 +125,7 @@ gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict
         }
     };
 
-    // acc is added into sum every F_CHAIN K tiles
+    // acc is added into sum every 3 or 4 K tiles
     f32x4_t acc[TM][TN], sum[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -239,26 +241,30 @@ gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict
     read_w(st[0]);
     read_a(st[0], 0, a0);
     widen_w();
-    constexpr int TURNS = F_CHAIN / S; // ring turns of a chain
-    int t = 0, turn = 0;
-    for (; t + S <= nk; t += S) {
+    // a turn: the chains' flush, in one block with the MFMAs that begin the next chain (from zero, so acc is
+    // not cleared, and the additions run under them), and 3, 4 or 6 K tiles, with a flush between the halves of 6
+    constexpr int TURN = S == 2 ? 4 : S;
+    constexpr bool HALF = TURN > F_CHAIN;
+    static_assert((HALF ? TURN / 2 : TURN) <= F_CHAIN, "chains too long");
+    int t = 0;
+    for (; t + TURN <= nk; t += TURN) {
+        flush();
         step(t, F_IC(0));
         step(t + 1, F_IC(1));
-        if constexpr (S > 2) step(t + 2, F_IC(2));
-        if constexpr (S > 3) step(t + 3, F_IC(3));
-        if constexpr (S > 4) step(t + 4, F_IC(4));
-        if constexpr (S > 5) step(t + 5, F_IC(5));
-        if (++turn == TURNS) {
-            flush();
-            turn = 0;
-        }
+        step(t + 2, F_IC(2 % S));
+        if constexpr (HALF) flush();
+        if constexpr (TURN > 3) step(t + 3, F_IC(3 % S));
+        if constexpr (TURN > 4) step(t + 4, F_IC(4 % S));
+        if constexpr (TURN > 5) step(t + 5, F_IC(5 % S));
     }
     // the last, partial turn
+    flush();
     if (t < nk) step(t, F_IC(0));
-    if constexpr (S > 2) if (t + 1 < nk) step(t + 1, F_IC(1));
-    if constexpr (S > 3) if (t + 2 < nk) step(t + 2, F_IC(2));
-    if constexpr (S > 4) if (t + 3 < nk) step(t + 3, F_IC(3));
-    if constexpr (S > 5) if (t + 4 < nk) step(t + 4, F_IC(4));
+    if (t + 1 < nk) step(t + 1, F_IC(1));
+    if constexpr (TURN > 3) if (t + 2 < nk) step(t + 2, F_IC(2 % S));
+    if constexpr (HALF) flush();
+    if constexpr (TURN > 4) if (t + 3 < nk) step(t + 3, F_IC(3 % S));
+    if constexpr (TURN > 5) if (t + 4 < nk) step(t + 4, F_IC(4 % S));
 #undef F_IC
     wait_vmem<0>(); // loads past the last tile (zeros) have landed before the workgroup ends
     flush();
