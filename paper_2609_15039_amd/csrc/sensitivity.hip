@@ -691,7 +691,9 @@ __global__ void __launch_bounds__(PI_NT) px_clear_kernel(unsigned* __restrict__ 
 }
 
 // Rows per workgroup of the resident kernel: the fewest instantiated ones that cover N with at
-// most 256 workgroups; 0 where the registers do not hold the matrix.
+// most 128 workgroups, or the most if that takes up to 256; 0 where the registers do not hold the
+// matrix.  The exchanges grow with the workgroups, the arithmetic hardly counts: 1024 x 2560 takes 9.9 us a
+// round on 256, 7.8 on 128 and 7.5 on 64, 4096 x 2560 10.5, 9.1 and 11.0.
 int px_rows(int64_t N, int64_t K, bool bf16)
 {
     static const int R1[] = {4, 8, 16, 24, 32, 40, 0}, R2[] = {4, 8, 12, 16, 20, 0}, R3[] = {4, 8, 12, 0}, R4[] = {4, 8, 0};
@@ -700,9 +702,13 @@ int px_rows(int64_t N, int64_t K, bool bf16)
     const int* l = bf16 ? (ch == 1 ? R1 : ch == 2 ? R2 : ch == 3 ? R3 : R4) : (ch == 1 ? F1 : ch == 2 ? F2 : F3);
     if (ch < 1 || ch > 4) return 0;
     for (; *l; ++l)
-        if ((N + *l - 1) / *l <= PX_MAX_WGS) return *l;
+        if ((N + *l - 1) / *l <= (l[1] ? PX_MAX_WGS / 2 : PX_MAX_WGS)) return *l;
     return 0;
 }
+
+// Rounds from which the resident kernel pays: its cooperative launch costs 25 us once, and a round saves 4-7 us
+// of 10-20 from 10 M elements up and up to 1024 columns, 1-2 us of 9 between (512 x 4096: 8.1 against 9.0 us).
+bool px_pays(int64_t N, int64_t K, int iters) { return iters >= (N * K >= 10000000 || K <= 1024 ? 8 : 24); }
 
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -864,7 +870,8 @@ int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int6
 {
     const bool bf16 = w_type == SPLITEE_BF16;
     bool gave_up = false;
-    int rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, px_rows(N, K, bf16), &gave_up, s);
+    int rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, px_pays(N, K, iters) ? px_rows(N, K, bf16) : 0,
+                          &gave_up, s);
     if (rc == SPLITEE_OK && gave_up)
         rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, 0, &gave_up, s);
     return rc;
