@@ -466,7 +466,7 @@ def fp_error_table(torch, sp, WL, O, np, projs, M, workload, deltas=None, nrows=
             "seconds": round(time.perf_counter() - t0, 1), "table": table}
 
 
-GEMM_SOURCES = ["paper_2609_15039_amd/csrc/gemm.hip", "paper_2609_15039_amd/csrc/common.hpp"]
+GEMM_SOURCES = ["paper_2609_15039_amd/csrc/" + f for f in ("gemm.hip", "gemm_dev.hpp", "common.hpp")]
 
 
 def gemm_source_sha():
@@ -595,7 +595,7 @@ def noise_scale_leg(torch, sp, WL, workload, iters):
     return {"model": model.name, "iters": iters, "sigma": {k: round(v, 6) for k, v in sig.items()},
             "delta": {k: float("%.6g" % v) for k, v in delta.items()},
             "round_us": round_us,
-            "roofline": {"bound": "hbm", "kernel": "power-method round (pi_round + pi_reduce), %s %dx%d bf16"
+            "roofline": {"bound": "hbm", "kernel": "power-method round, %s %dx%d bf16"
                          % ((big,) + tuple(Ws[big].shape)),
                          "achieved": gbs[big], "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(gbs[big] / HBM_PEAK_GBS, 4),

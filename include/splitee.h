@@ -202,7 +202,8 @@ int splitee_tile_weights(const void* W, int64_t ldw, int64_t N, int64_t K, void*
  *   W      N x K, w_type float32, bfloat16 (ldw) or tiled bfloat16; BF16 / BF16X3 need
  *          bfloat16 W, F32 takes row-major W
  *   R      out, M x N float32 (ldr)
- * Requires K % 8 == 0.  Needs no workspace (single-pass K reduction per tile).
+ * Requires K % 8 == 0.  Needs no workspace (one launch; a tile's K reduction stays in one
+ * workgroup).
  */
 int splitee_masked_linear(const void* Xt, int in_prec, int64_t ldxt, const void* W, int w_type,
                           int64_t ldw, float* R, int64_t ldr, int64_t M, int64_t N, int64_t K,
@@ -251,8 +252,8 @@ size_t splitee_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec);
  * M <= 16 with BF16 or BF16X3 takes the bandwidth-bound decode kernels (M <= 2: a
  * vector-ALU GEMV, on whole rows of row-major W or 32-row blocks of tiled W; else
  * the skinny MFMA kernel); given eta_override they form fl32(X + eta) and its
- * bfloat16 planes themselves (one launch, bit-identical to the two-launch path).  Otherwise the tiled
- * or W-streamed MFMA kernel runs, split over K when the tile count is small; for
+ * bfloat16 planes themselves (one launch, bit-identical to the two-launch path).  Otherwise the
+ * binary32 or the W-streamed bfloat16 MFMA kernel runs, split over K when the tile count is small; for
  * 17 <= M <= 128 on tiled W given eta_override, the streamed kernel too forms the masked
  * input itself (bit-identical to the mask launch followed by the GEMM).
  * workspace: >= splitee_fused_workspace_bytes(M, N, K, prec) bytes, 256-byte
