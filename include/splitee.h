@@ -228,7 +228,7 @@ size_t splitee_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec);
  * over K; the partial tiles are summed in split order (by a second kernel, or by
  * the last workgroup of each tile), so results are deterministic.  workspace: >=
  * splitee_gemm_workspace_bytes bytes, 256-byte aligned, zero-filled before its
- * first use (calls leave it zeroed).  Requires K % 8 == 0.
+ * first use and then shared freely (see splitee_masked_linear_fused).  Requires K % 8 == 0.
  */
 int splitee_masked_linear_unmask(const void* Xt, int in_prec, int64_t ldxt, const void* W,
                                  int w_type, int64_t ldw, const float* C, int64_t ldc, float* Y,
@@ -257,7 +257,13 @@ size_t splitee_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec);
  * 17 <= M <= 128 on tiled W given eta_override, the streamed kernel too forms the masked
  * input itself (bit-identical to the mask launch followed by the GEMM).
  * workspace: >= splitee_fused_workspace_bytes(M, N, K, prec) bytes, 256-byte
- * aligned; it must hold zeros before its first use and calls leave it that way.
+ * aligned, zero-filled before its first use.  Its first 128 KiB are tile counters, which every
+ * call leaves zero; the rest needs no contents.  One workspace therefore serves calls of
+ * this function, splitee_correction and splitee_masked_linear_unmask of any shapes, precisions and
+ * weight layouts one after another (calls that overlap in time need one each), if it is as
+ * large as the query says for each of them: fewer rows can need more bytes than many (a K split
+ * that fills the chip).  Calls whose workspace needs no contents (binary64, spectral norm,
+ * sensitivity) overwrite it all: zero the 128 KiB again after them.
  */
 int splitee_masked_linear_fused(const float* X, int64_t ldx, const void* W, int w_type, int64_t ldw,
                                 const float* C, int64_t ldc, float* Y, int64_t ldy, int64_t M,
@@ -277,7 +283,7 @@ int splitee_masked_linear_fused(const float* X, int64_t ldx, const void* W, int 
  * nothing: on its first use on a device it looks up that device's copy of the buffer,
  * and it clears the split-K counters on `stream` itself.
  *   SPLITEE_ERR_SCRATCH   the shape needs more scratch than the buffer holds (the
- *                         workspace splitee_fused_workspace_bytes would ask for, roughly
+ *                         workspace splitee_fused_workspace_bytes would ask for behind its counters, roughly
  *                         M K 6 bytes for BF16X3 plus the split-K partials): use
  *                         splitee_masked_linear_fused with a caller-owned workspace
  *   SPLITEE_ERR_HIP       the buffer could not be resolved on the current device

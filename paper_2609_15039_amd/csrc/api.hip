@@ -50,11 +50,22 @@ inline bool valid_dtype(int t) { return t == SPLITEE_F32 || t == SPLITEE_BF16 ||
 // Skinny kernel for decode-sized M with bfloat16 operands, tiled kernel otherwise.
 inline bool use_skinny(int64_t M, int prec) { return M <= 16 && prec != SPLITEE_PREC_F32; }
 
+// Bytes of the GEMM's split-K partials.
 size_t gemm_ws(int64_t M, int64_t N, int64_t K, int prec, int w_type)
 {
     return use_skinny(M, prec) ? splitee_host::skinny_workspace_bytes(M, N, K, prec, w_type)
                                : splitee_host::gemm_workspace_bytes(M, N, K, prec, w_type);
 }
+// The GEMM's part of a workspace, counters included; 0 when none is needed.
+size_t gemm_ws_bytes(size_t part) { return part ? splitee::WS_COUNTER_BYTES + part : 0; }
+
+// Counters, partials and masked input (prec planes of M x K).
+size_t fused_ws_bytes(size_t part, int64_t M, int64_t K, int prec)
+{
+    const size_t b = align256(part) + align256((size_t)(prec_planes(prec) * M * K * prec_elsize(prec)));
+    return b ? splitee::WS_COUNTER_BYTES + b : 0;
+}
+
 // Workspace queries take no weight layout: the larger of the row-major and the
 // tiled plan (the float32 MFMA path reads row-major W only).
 size_t gemm_ws_any(int64_t M, int64_t N, int64_t K, int prec)
@@ -102,8 +113,8 @@ int run_masked(const float* X, int64_t ldx, const void* W, int w_type, int64_t l
                double sensitivity, double epsilon, uint64_t seed, uint64_t sid, uint64_t row0,
                const float* eta_override, int prec, void* ws, size_t ws_bytes, hipStream_t s)
 {
-    const size_t gws = align256(gemm_ws(M, N, K, prec, w_type));
-    const size_t need = gws + align256((size_t)(prec_planes(prec) * M * K * prec_elsize(prec)));
+    const size_t part = gemm_ws(M, N, K, prec, w_type);
+    const size_t gws = splitee::WS_COUNTER_BYTES + align256(part), need = fused_ws_bytes(part, M, K, prec);
     if (ws_bytes < need || (need > 0 && ws == nullptr)) return SPLITEE_ERR_WORKSPACE;
     if (ws && (reinterpret_cast<uintptr_t>(ws) & 255u)) return SPLITEE_ERR_ALIGN;
     if (M == 0 || N == 0) return SPLITEE_OK;
@@ -169,7 +180,9 @@ int check_w_f64(const void* W, int w_type, int64_t ldw, int64_t K)
 // array's name to a kernel -- on the host it is only a stand-in symbol -- but the
 // device address hipGetSymbolAddress returns for the current device, looked up once
 // per device and kept.
-static __device__ __align__(256) unsigned char scratch[SPLITEE_NOALLOC_SCRATCH_BYTES];
+// The counters lie in front of the SPLITEE_NOALLOC_SCRATCH_BYTES.
+constexpr size_t SCRATCH_BYTES = splitee::WS_COUNTER_BYTES + SPLITEE_NOALLOC_SCRATCH_BYTES;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 constexpr int SCRATCH_MAX_DEVICES = 64;
 std::mutex scratch_mutex;
@@ -346,7 +359,7 @@ int splitee_unmask(const float* R, int64_t ldr, const float* C, int64_t ldc, flo
 size_t splitee_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec)
 {
     if (!valid_prec(prec) || !dims_ok(M, N, K) || K % 8 != 0) return 0;
-    return gemm_ws_any(M, N, K, prec);
+    return gemm_ws_bytes(gemm_ws_any(M, N, K, prec));
 }
 
 int splitee_masked_linear_unmask(const void* Xt, int in_prec, int64_t ldxt, const void* W,
@@ -358,7 +371,7 @@ int splitee_masked_linear_unmask(const void* Xt, int in_prec, int64_t ldxt, cons
     if (!dims_ok(M, N, K) || K % 8 != 0 || ldxt < K || ldy < N || (C && ldc < N)) return SPLITEE_ERR_SHAPE;
     int rc = check_w(W, w_type, ldw, K, in_prec);
     if (rc) return rc;
-    const size_t need = gemm_ws(M, N, K, in_prec, w_type);
+    const size_t need = gemm_ws_bytes(gemm_ws(M, N, K, in_prec, w_type));
     if (workspace_bytes < need || (need > 0 && workspace == nullptr)) return SPLITEE_ERR_WORKSPACE;
     if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u)) return SPLITEE_ERR_ALIGN;
     if (M == 0 || N == 0) return SPLITEE_OK;
@@ -373,8 +386,7 @@ int splitee_masked_linear_unmask(const void* Xt, int in_prec, int64_t ldxt, cons
 size_t splitee_fused_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec)
 {
     if (!valid_prec(prec) || !dims_ok(M, N, K) || K % 8 != 0) return 0;
-    return align256(gemm_ws_any(M, N, K, prec)) +
-           align256((size_t)(prec_planes(prec) * M * K * prec_elsize(prec)));
+    return fused_ws_bytes(gemm_ws_any(M, N, K, prec), M, K, prec);
 }
 
 int splitee_masked_linear_fused(const float* X, int64_t ldx, const void* W, int w_type, int64_t ldw,
@@ -419,9 +431,7 @@ int splitee_masked_linear_fused_noalloc(const float* X, int64_t ldx, const void*
     if (!aligned16(X) || !pitch16(ldx, 4) || !aligned16(C) || !pitch16(ldc, 4) || !aligned16(Y) ||
         !pitch16(ldy, 4) || (eta_override && !aligned16(eta_override)))
         return SPLITEE_ERR_ALIGN;
-    const size_t need = align256(gemm_ws(M, N, K, prec, w_type)) +
-                        align256((size_t)(prec_planes(prec) * M * K * prec_elsize(prec)));
-    if (need > (size_t)SPLITEE_NOALLOC_SCRATCH_BYTES) return SPLITEE_ERR_SCRATCH;
+    if (fused_ws_bytes(gemm_ws(M, N, K, prec, w_type), M, K, prec) > SCRATCH_BYTES) return SPLITEE_ERR_SCRATCH;
     void* ws = scratch_for_current_device();
     if (!ws) return SPLITEE_ERR_HIP;
     hipStream_t s = as_stream(stream);
@@ -436,7 +446,7 @@ int splitee_masked_linear_fused_noalloc(const float* X, int64_t ldx, const void*
         if (hipGetLastError() != hipSuccess) return SPLITEE_ERR_HIP;
     }
     return run_masked(X, ldx, W, w_type, ldw, C, ldc, Y, ldy, M, N, K, mech, sensitivity, epsilon, seed, stream_id,
-                      row0, eta_override, prec, ws, (size_t)SPLITEE_NOALLOC_SCRATCH_BYTES, s);
+                      row0, eta_override, prec, ws, SCRATCH_BYTES, s);
 }
 
 int splitee_correction(float* C, int64_t ldc, const void* W, int w_type, int64_t ldw, int64_t M,

@@ -14,6 +14,13 @@ namespace splitee {
 // most noise blocks one splitee_noise_gen_multi call generates
 constexpr int NOISE_MULTI_MAX = 8;
 
+// The split-K tile counters of the decode kernels are the first bytes of a workspace.  They are
+// zeros between calls (a tile's last workgroup resets its own), and no call writes anything else
+// there, whatever its shape and precision, so one workspace serves any sequence of calls: partials
+// and masked input begin behind them.  32768 counters are all that a W below the 2 GB of a buffer
+// resource needs: more 64-column tiles (or 32-row blocks) leave K < 512 (1024), which is not split.
+constexpr size_t WS_COUNTER_BYTES = 128 * 1024;
+
 // Bytes of a bfloat16 N x K weight matrix in the tiled order: 32-row blocks of
 // 64-k tiles, 4 KB each, N padded to a multiple of 32 and K to a multiple of 64.
 inline size_t tiled_weights_bytes(int64_t N, int64_t K)
@@ -78,6 +85,8 @@ __device__ __forceinline__ uint32_t xcd_logical_block(uint32_t b, uint32_t nbloc
 
 // host-side launch helpers implemented in the kernel translation units
 namespace splitee_host {
+// Where a GEMM's split-K partials begin in a workspace.
+inline float* ws_partials(void* ws) { return reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + splitee::WS_COUNTER_BYTES); }
 int launch_noise(float* eta, int64_t ld_eta, int64_t M, int64_t K, int mech, double scale,
                  uint64_t seed, uint64_t sid, uint64_t row0, hipStream_t s);
 int launch_noise_multi(float* const* eta, const int64_t* ld, const int64_t* K, const uint64_t* sid, int count,
@@ -91,7 +100,9 @@ int launch_unmask(const float* R, int64_t ldr, const float* C, int64_t ldc, floa
                   int64_t M, int64_t N, hipStream_t s);
 int launch_transform_probe(const uint32_t* w, int64_t n, int fn, int force_slow, float* out,
                            hipStream_t s);
-// Tiled MFMA GEMM: Out = A . W^T (- C if C != nullptr), A given as prec planes.
+// Tiled MFMA GEMM: Out = A . W^T (- C if C != nullptr), A given as prec planes.  A workspace
+// here and below is the caller's, counters first; gemm_workspace_bytes and skinny_workspace_bytes are
+// the bytes of the partials behind them.
 size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_type);
 int launch_gemm(const void* A, int prec, int64_t lda, int64_t plane_stride, const void* W,
                 int w_type, int64_t ldw, const float* C, int64_t ldc, float* Out, int64_t ldo,

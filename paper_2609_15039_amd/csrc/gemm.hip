@@ -1690,7 +1690,7 @@ int launch_gemm(const void* A, int prec, int64_t lda, int64_t pstride, const voi
                                ws_bytes, s);
     const bool allow_split = ws != nullptr;
     Plan p = plan_stream(M, N, K, prec, w_type, allow_split);
-    if (p.ksplit > 1 && ws_bytes < p.part_bytes) return SPLITEE_ERR_WORKSPACE;
+    if (p.ksplit > 1 && ws_bytes < splitee::WS_COUNTER_BYTES + p.part_bytes) return SPLITEE_ERR_WORKSPACE;
     dim3 grid((unsigned)(p.mtiles * p.ntiles * p.ksplit));
     const int m = (int)M, n = (int)N, k = (int)K;
     const uint16_t* a = reinterpret_cast<const uint16_t*>(A);
@@ -1708,7 +1708,7 @@ int launch_gemm(const void* A, int prec, int64_t lda, int64_t pstride, const voi
         if (M <= WSPLIT_MAX_M && plan_wsplit(M, N, prec, w_type).cost < unsplit_cost(p, prec))
             return launch_wsplit(A, prec, lda, pstride, W, w_type, ldw, C, ldc, Out, ldo, M, N, K, s);
     }
-    float* pp = reinterpret_cast<float*>(ws);
+    float* pp = ws ? ws_partials(ws) : nullptr;
 #define ST_LAUNCH(NP, BM_, BN_, WGM_, D_, NW_, T_) hipLaunchKernelGGL((gemm_stream_kernel<NP, BM_, BN_, WGM_, D_, NW_, T_>), grid, dim3(NW_ * WAVE), 0, s, a, lda, pstride, w, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, pp)
 #define ST_SUM(BM_, BN_, WGM_, WGN_) hipLaunchKernelGGL((stream_sum_kernel<BM_, BN_, WGM_, WGN_>), g2, dim3(256), 0, s, pp, p.ksplit, C, ldc, Out, ldo, m, n, p.mtiles, tiles)
     switch (p.variant) {
@@ -1754,10 +1754,9 @@ size_t skinny_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_t
 {
     if (w_type == SPLITEE_BF16_TILED && M <= GV_MMAX) {
         const GtPlan g = plan_gemv_tiled(M, N, K);
-        return g.counter_bytes + g.part_bytes;
+        return g.part_bytes;
     }
-    Plan p = plan_skinny(M, N, K, prec);
-    return p.counter_bytes + p.part_bytes;
+    return plan_skinny(M, N, K, prec).part_bytes;
 }
 
 size_t skinny_counter_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_type)
@@ -1775,9 +1774,10 @@ int run_skinny(const SkSrc& src, int prec, const void* W, bool tiled, int64_t ld
     Plan p = plan_skinny(M, N, K, prec);
     const size_t lds = skinny_lds_bytes(M, npl, p.kt_per_split);
     if (lds > (size_t)SK_LDS_MAX) return SPLITEE_ERR_UNSUPPORTED;
-    if (p.ksplit > 1 && (ws == nullptr || ws_bytes < p.counter_bytes + p.part_bytes)) return SPLITEE_ERR_WORKSPACE;
+    if (p.ksplit > 1 && (ws == nullptr || ws_bytes < splitee::WS_COUNTER_BYTES + p.part_bytes)) return SPLITEE_ERR_WORKSPACE;
+    if (p.counter_bytes > splitee::WS_COUNTER_BYTES) return SPLITEE_ERR_UNSUPPORTED; // W past 2 GB, refused before
     unsigned* counters = p.ksplit > 1 ? reinterpret_cast<unsigned*>(ws) : nullptr;
-    float* part = p.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.counter_bytes) : nullptr;
+    float* part = p.ksplit > 1 ? ws_partials(ws) : nullptr;
     dim3 grid((unsigned)(p.ntiles * p.ksplit));
     const uint16_t* w = reinterpret_cast<const uint16_t*>(W);
 #define SK_LAUNCHR(NP, RR, T, MC) hipLaunchKernelGGL((skinny_kernel<NP, RR, MASK, T, MC>), grid, dim3(256), lds, s, src, w, ldw, C, ldc, Out, ldo, (int)M, (int)N, (int)K, p.ntiles, p.ksplit, p.kt_per_split, part, counters)
@@ -1800,9 +1800,10 @@ int run_gemv_tiled(const SkSrc& src, int prec, const void* W, const float* C, in
 {
     const GtPlan p = plan_gemv_tiled(M, N, K);
     if (p.lds > (size_t)GT_LDS_MAX) return SPLITEE_ERR_UNSUPPORTED;
-    if (p.ksplit > 1 && (ws == nullptr || ws_bytes < p.counter_bytes + p.part_bytes)) return SPLITEE_ERR_WORKSPACE;
+    if (p.ksplit > 1 && (ws == nullptr || ws_bytes < splitee::WS_COUNTER_BYTES + p.part_bytes)) return SPLITEE_ERR_WORKSPACE;
+    if (p.counter_bytes > splitee::WS_COUNTER_BYTES) return SPLITEE_ERR_UNSUPPORTED; // W past 2 GB, refused before
     unsigned* counters = p.ksplit > 1 ? reinterpret_cast<unsigned*>(ws) : nullptr;
-    float* part = p.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.counter_bytes) : nullptr;
+    float* part = p.ksplit > 1 ? ws_partials(ws) : nullptr;
     const dim3 grid((unsigned)((int64_t)p.nblocks * p.ksplit));
     const uint16_t* w = reinterpret_cast<const uint16_t*>(W);
 #define GT_LAUNCH(NP, MR) hipLaunchKernelGGL((gemv_tiled_kernel<NP, MASK, MR>), grid, dim3(GV_WAVES * WAVE), p.lds, s, src, w, C, ldc, Out, ldo, (int)N, (int)K, p.nblocks, p.ksplit, p.kt_per_split, part, counters)
@@ -1869,9 +1870,9 @@ int launch_gemm_masked(const float* X, int64_t ldx, const float* eta, int64_t ld
     const bool allow_split = ws != nullptr;
     Plan p = plan_stream(M, N, K, prec, w_type, allow_split);
     if (p.variant != 24 && p.variant != 25 && p.variant != 26 && p.variant != 27) return SPLITEE_ERR_UNSUPPORTED;
-    if (p.ksplit > 1 && ws_bytes < p.part_bytes) return SPLITEE_ERR_WORKSPACE;
+    if (p.ksplit > 1 && ws_bytes < splitee::WS_COUNTER_BYTES + p.part_bytes) return SPLITEE_ERR_WORKSPACE;
     if (p.part_bytes >= (size_t(1) << 31)) return SPLITEE_ERR_UNSUPPORTED; // the sum kernel's buffer offsets
-    float* pp = reinterpret_cast<float*>(ws);
+    float* pp = ws ? ws_partials(ws) : nullptr;
     const uint16_t* w = reinterpret_cast<const uint16_t*>(W);
     dim3 grid((unsigned)(p.mtiles * p.ntiles * p.ksplit));
     const int m = (int)M, n = (int)N, k = (int)K;

@@ -343,7 +343,7 @@ f32_sum_kernel(const float* __restrict__ part, int ksplit, const float* __restri
 struct F32Plan {
     int tm, tn, mtiles;
     int nfull, rem, ksplit, ktps; // whole tiles, split tiles, their splits and K tiles per split
-    size_t part_off, part_bytes;  // in the workspace
+    size_t part_bytes;
 };
 
 constexpr size_t F32_SCRATCH = SPLITEE_NOALLOC_SCRATCH_BYTES; // partials and the masked input together
@@ -359,9 +359,6 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, bool allow_split)
 {
     const int ktiles = (int)((K + F_BK - 1) / F_BK);
     const size_t xt = ((size_t)M * K * 4 + 255) / 256 * 256;
-    // the decode kernels keep their tile counters (at most one per 32 columns) at the workspace's
-    // start and expect zeros there: the partials begin behind them
-    const size_t off = ((size_t)((N + 31) / 32) * 4 + 255) / 256 * 256;
     F32Plan best{};
     double best_cost = -1.0;
     // (rows that one more 16-row block would only pad are not tried: the planning costs host time)
@@ -377,7 +374,7 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, bool allow_split)
                 const int ktps = ktiles > 0 ? (ktiles + ks - 1) / ks : 1;
                 if (ks > 1 && (ktiles + ktps - 1) / ktps != ks) continue;
                 const size_t pb = ks > 1 ? (size_t)rem * ks * tm * tn * 4096 : 0;
-                if (ks > 1 && off + pb + xt + 512 > F32_SCRATCH) break;
+                if (ks > 1 && pb + xt + 512 > F32_SCRATCH) break;
                 const int64_t wgs = rem * ks, rounds = (wgs + 255) / 256;
                 const double alone = full == 0 && wgs <= 256 ? 1.05 : 1.0;
                 const double cost = (double)(full / 256) * (ktiles * ktile + 1.0) +
@@ -391,7 +388,6 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, bool allow_split)
                 best.ktps = ktps;
                 best.rem = (int)(ks > 1 ? rem : 0);
                 best.nfull = (int)(ks > 1 ? full : tiles);
-                best.part_off = ks > 1 ? off : 0;
                 best.part_bytes = pb;
             }
         }
@@ -402,11 +398,9 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, bool allow_split)
 
 namespace splitee_host {
 
-size_t f32_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K) 
+size_t f32_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K)
 {
-    if (M == 0 || N == 0) return 0;
-    const F32Plan p = plan_f32(M, N, K, true);
-    return p.part_off + p.part_bytes;
+    return M > 0 && N > 0 ? plan_f32(M, N, K, true).part_bytes : 0;
 }
 
 int launch_gemm_f32(const float* A, int64_t lda, const void* W, int w_type, int64_t ldw, const float* C, int64_t ldc,
@@ -414,8 +408,8 @@ int launch_gemm_f32(const float* A, int64_t lda, const void* W, int w_type, int6
 {
     if (M == 0 || N == 0) return SPLITEE_OK;
     const F32Plan p = plan_f32(M, N, K, ws != nullptr);
-    if (p.ksplit > 1 && ws_bytes < p.part_off + p.part_bytes) return SPLITEE_ERR_WORKSPACE;
-    float* part = p.ksplit > 1 ? reinterpret_cast<float*>(reinterpret_cast<char*>(ws) + p.part_off) : nullptr;
+    if (p.ksplit > 1 && ws_bytes < splitee::WS_COUNTER_BYTES + p.part_bytes) return SPLITEE_ERR_WORKSPACE;
+    float* part = p.ksplit > 1 ? ws_partials(ws) : nullptr;
     const dim3 grid((unsigned)(p.nfull + (int64_t)p.rem * p.ksplit));
     const dim3 g2((unsigned)(((int64_t)p.rem * p.tm * p.tn * 256 + 255) / 256));
     const bool bf16 = w_type == SPLITEE_BF16;
