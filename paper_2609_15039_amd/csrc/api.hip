@@ -53,6 +53,7 @@ inline bool use_skinny(int64_t M, int prec) { return M <= 16 && prec != SPLITEE_
 // Bytes of the GEMM's split-K partials.
 size_t gemm_ws(int64_t M, int64_t N, int64_t K, int prec, int w_type)
 {
+    if (M == 0 || N == 0) return 0; // no tiles to plan
     return use_skinny(M, prec) ? splitee_host::skinny_workspace_bytes(M, N, K, prec, w_type)
                                : splitee_host::gemm_workspace_bytes(M, N, K, prec, w_type);
 }
