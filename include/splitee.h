@@ -444,8 +444,8 @@ typedef struct {
  * bytes, NUL-terminated); SPLITEE_ERR_ARG if it does not fit. */
 int splitee_bank_path(const char* dir, int64_t K, int64_t N, uint64_t stream_id, char* out, size_t out_len);
 
-/* Device workspace bytes splitee_bank_create needs: the fused call's workspace for 256
- * rows plus a 256 x N float32 staging block; 0 on invalid arguments. */
+/* Device workspace bytes splitee_bank_create needs: the fused call's largest
+ * workspace for 1 to 256 rows plus a 256 x N float32 staging block; 0 on invalid arguments. */
 size_t splitee_bank_workspace_bytes(int64_t K, int64_t N, int prec);
 
 /*

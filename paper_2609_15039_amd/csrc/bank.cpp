@@ -53,6 +53,16 @@ struct Header {
 static_assert(sizeof(Header) == BANK_HEADER, "bank header is 128 bytes");
 static_assert(offsetof(Header, consumed) == CONSUMED_OFFSET, "watermark offset");
 
+// Workspace of the corrections of any chunk: the last one can be short, and fewer rows can need
+// more bytes than BANK_CHUNK (their K is split where that of more tiles is not).  0 on invalid arguments.
+size_t chunk_workspace_bytes(int64_t K, int64_t N, int prec)
+{
+    size_t most = 0;
+    for (int64_t rows = 1; rows <= BANK_CHUNK; ++rows)
+        most = std::max(most, splitee_fused_workspace_bytes(rows, N, K, prec));
+    return most;
+}
+
 bool full_pwrite(int fd, const void* buf, size_t n, off_t off)
 {
     const char* p = static_cast<const char*>(buf);
@@ -117,7 +127,7 @@ int splitee_bank_path(const char* dir, int64_t K, int64_t N, uint64_t stream_id,
 size_t splitee_bank_workspace_bytes(int64_t K, int64_t N, int prec)
 {
     if (prec != SPLITEE_PREC_F32 && prec != SPLITEE_PREC_BF16X3) return 0;  // the corrections' modes
-    const size_t fused = splitee_fused_workspace_bytes(BANK_CHUNK, N, K, prec);
+    const size_t fused = chunk_workspace_bytes(K, N, prec);
     if (fused == 0) return 0;
     return fused + (size_t)BANK_CHUNK * (size_t)N * 4;
 }
@@ -129,14 +139,14 @@ int splitee_bank_create(const char* path, const void* W, int w_type, int64_t ldw
     if (!path || rows < 0 || (int64_t)row0 < 0) return SPLITEE_ERR_ARG;
     if (N <= 0 || K < 0 || N > BANK_MAX_DIM || K > BANK_MAX_DIM || N % 4 != 0) return SPLITEE_ERR_SHAPE;
     // validate every argument of the correction before touching the file system
-    const size_t fused = splitee_fused_workspace_bytes(BANK_CHUNK, N, K, prec);
+    const size_t fused = chunk_workspace_bytes(K, N, prec);
     if (fused == 0) return prec == SPLITEE_PREC_F32 || prec == SPLITEE_PREC_BF16X3 ? SPLITEE_ERR_SHAPE
                                                                                    : SPLITEE_ERR_UNSUPPORTED;
     int rc = splitee_correction(nullptr, N, W, w_type, ldw, 0, N, K, mech, sensitivity, epsilon, seed, stream_id,
                                 row0, prec, nullptr, 0, stream);
     if (rc) return rc;
     if (rows > 0 && !W) return SPLITEE_ERR_ARG;
-    if (rows > 0 && (!workspace || workspace_bytes < splitee_bank_workspace_bytes(K, N, prec)))
+    if (rows > 0 && (!workspace || workspace_bytes < fused + (size_t)BANK_CHUNK * (size_t)N * 4))
         return SPLITEE_ERR_WORKSPACE;
     if (workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u)) return SPLITEE_ERR_ALIGN;
 
