@@ -9,8 +9,14 @@
 // ahead, swizzled, one barrier per K tile in the middle of its MFMAs, fragments read half a tile
 // ahead.  W is converted as its fragments leave LDS.  Before, each 16-k tile went through
 // registers into rows padded by one element, with four MFMAs per barrier and k.
-// Llama-3.2-3B Down through the fused call: 128 tokens 190 -> 123 us (52 TFLOP/s), 256 tokens 365 -> 220,
+// Llama-3.2-3B Down through the fused call: 128 tokens 190 -> 117 us (55 TFLOP/s), 256 tokens 365 -> 220,
 // one token 100 -> 26; 250 x 700 x 1024 28.2 -> 19.4 us.
+//
+// An accumulator chain runs over 96 or 128 k and is then added into a second set of registers, as in the binary32
+// GEMM.  Distance from the 64-bit result at noise of 1.66e8, mean over 1-250 tokens x 300-3072 columns, with
+// the former K splits, with chains of 384 k and so: K = 264 7.6e-8, 1.03e-7, 7.4e-8; 768 7.7e-8, 9.3e-8, 7.5e-8;
+// 9728 1.6e-7, 1.2e-7, 8.0e-8.  The additions run under the next chain's first MFMAs and cost nothing (384-k
+// chains added at their end: 119 us for the 117 above).
 #include "gemm_dev.hpp"
 
 #include <algorithm>
@@ -26,7 +32,7 @@ constexpr int D_NT = D_NW * WAVE;
 constexpr int D_BK = 32;          // k of one stage: 256 bytes of an A row
 constexpr int D_BN = 64;          // columns of a tile
 constexpr int D_MAX_TM = 4;       // 16-row blocks of a tile
-constexpr int D_CHAIN = 12;       // K tiles that one accumulator chain runs over
+constexpr int D_CHAIN = 4;        // K tiles that one accumulator chain runs over at most
 
 __device__ __attribute__((aligned(16))) const double f64_zeros[2] = {0.0, 0.0};
 
@@ -112,7 +118,7 @@ gemm_f64_kernel(const double* __restrict__ A, int64_t lda, const void* __restric
         }
     };
 
-    f64x4 acc[TM], sum[TM]; // acc is added into sum every D_CHAIN K tiles
+    f64x4 acc[TM], sum[TM]; // acc is added into sum every ring turn (3 or 4 K tiles)
 #pragma unroll
     for (int i = 0; i < TM; ++i) acc[i] = sum[i] = f64x4{0.0, 0.0, 0.0, 0.0};
 
@@ -214,19 +220,19 @@ gemm_f64_kernel(const double* __restrict__ A, int64_t lda, const void* __restric
     read_w(st[0]);
     read_a(st[0], 0, a0);
     widen_w(0);
-    constexpr int TURNS = D_CHAIN / S; // ring turns of a chain
-    int t = 0, turn = 0;
+    // a turn: the chains' flush, in one block with the MFMAs that begin the next chain (from zero, so acc is
+    // not cleared, and the additions run under them), then the ring's K tiles
+    static_assert(S <= D_CHAIN, "chains too long");
+    int t = 0;
     for (; t + S <= nk; t += S) {
+        flush();
         step(t, D_IC(0));
         step(t + 1, D_IC(1));
         step(t + 2, D_IC(2));
         if constexpr (S > 3) step(t + 3, D_IC(3));
-        if (++turn == TURNS) {
-            flush();
-            turn = 0;
-        }
     }
     // the last, partial turn
+    flush();
     if (t < nk) step(t, D_IC(0));
     if (t + 1 < nk) step(t + 1, D_IC(1));
     if constexpr (S > 3) if (t + 2 < nk) step(t + 2, D_IC(2));
