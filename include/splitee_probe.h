@@ -1,9 +1,10 @@
 /*
  * splitee_probe.h -- test hooks of libsplitee.so (not part of the masked-linear path).
  *
- * These two entry points let the tests look at the arithmetic the kernels are built
+ * Two entry points let the tests look at the arithmetic the kernels are built
  * on: the correctly rounded noise transforms, and the rounding of the matrix-core
- * (MFMA) instructions the GEMM kernels issue.  The error bounds that the tests
+ * (MFMA) instructions the GEMM kernels issue; a third tells which kernels a spectral norm
+ * took.  The error bounds that the tests
  * apply to the GEMM (the dot-product bound gamma_n of Def. 6 and Theorem 4) assume
  * that each floating-point operation rounds to nearest with unit roundoff u; the
  * MFMA probe lets a test check that assumption for each instruction on the device.
@@ -56,6 +57,22 @@ int splitee_transform_probe(const uint32_t* words, int64_t n, int fn, int force_
  * op outside 0..3, n outside 1..64 or a null pointer: SPLITEE_ERR_ARG.
  */
 int splitee_mfma_probe(int op, int n, const double* a, const double* b, double c, double* d, void* stream);
+
+/*
+ * splitee_spectral_norm, and what ran.
+ *   spins  tries after which a poll of the kernel that holds W in registers gives up (the
+ *          rounds then run again with W streamed); negative: the library's own bound
+ *   path   host, receives a splitee_spectral_path, or NULL
+ */
+typedef enum {
+    SPLITEE_PATH_NONE = 0,     /* an empty matrix or an error: no rounds ran */
+    SPLITEE_PATH_STREAMED = 1, /* two kernels a round, W read in each */
+    SPLITEE_PATH_RESIDENT = 2, /* one kernel for all rounds, W in registers */
+    SPLITEE_PATH_GAVE_UP = 3   /* that kernel gave up; the result is the streamed one */
+} splitee_spectral_path;
+int splitee_spectral_norm_probe(const void* W, int w_type, int64_t ldw, int64_t N, int64_t K, int iters,
+                                uint64_t seed, uint64_t stream_id, double* sigma, double* history,
+                                void* workspace, size_t workspace_bytes, int64_t spins, int* path, void* stream);
 
 #ifdef __cplusplus
 }

@@ -35,7 +35,8 @@ EXPORTED = [
     "splitee_tiled_weights_bytes", "splitee_tile_weights", "splitee_masked_linear_fused_noalloc",
 ]
 # test hooks (include/splitee_probe.h)
-EXPORTED_PROBE = ["splitee_transform_probe", "splitee_mfma_probe"]
+EXPORTED_PROBE = ["splitee_transform_probe", "splitee_mfma_probe", "splitee_spectral_norm_probe"]
+SPLITEE_PATH_NONE, SPLITEE_PATH_STREAMED, SPLITEE_PATH_RESIDENT, SPLITEE_PATH_GAVE_UP = 0, 1, 2, 3
 SPLITEE_PREC_F64 = 3
 SPLITEE_ERR_IO, SPLITEE_ERR_EXHAUSTED, SPLITEE_ERR_FORMAT, SPLITEE_ERR_BUSY = -8, -9, -10, -11
 SPLITEE_ERR_SCRATCH = -12
@@ -111,6 +112,7 @@ def load():
         "splitee_tiled_weights_bytes": (SZ, [I64, I64]),
         "splitee_tile_weights": (I, [P, I64, I64, I64, P, P]),
         "splitee_mfma_probe": (I, [I, I, P, P, D, P, P]),
+        "splitee_spectral_norm_probe": (I, [P, I, I64, I64, I64, I, U64, U64, P, P, P, SZ, I64, P, P]),
         "splitee_masked_linear_fused_noalloc": (I, [P, I64, P, I, I64, P, I64, P, I64, I64, I64, I64, I, D, D,
                                                     U64, U64, U64, P, I, P]),
     }
@@ -319,6 +321,17 @@ def splitee_spectral_norm(W, w_type, ldw, N, K, iters, seed, stream_id, workspac
         ctypes.cast(hist, ctypes.c_void_p) if hist is not None else None, _ptr(workspace), workspace_bytes,
         _stream(stream)))
     return (sigma.value, list(hist) if hist is not None else []) if history else sigma.value
+
+
+def splitee_spectral_norm_probe(W, w_type, ldw, N, K, iters, seed, stream_id, workspace, workspace_bytes, spins=-1,
+                                stream=None):
+    """Returns (path, [sigma of every round]); path as splitee_spectral_path."""
+    sigma, path, hist = ctypes.c_double(), ctypes.c_int(), (ctypes.c_double * iters)()
+    _check("splitee_spectral_norm_probe", load().splitee_spectral_norm_probe(
+        _ptr(W), w_type, ldw, N, K, iters, seed, stream_id, ctypes.byref(sigma),
+        ctypes.cast(hist, ctypes.c_void_p), _ptr(workspace), workspace_bytes, spins, ctypes.byref(path),
+        _stream(stream)))
+    return path.value, list(hist)
 
 
 def splitee_sensitivity_workspace_bytes():

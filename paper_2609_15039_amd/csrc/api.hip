@@ -528,6 +528,16 @@ int splitee_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int
                           uint64_t seed, uint64_t stream_id, double* sigma, double* history,
                           void* workspace, size_t workspace_bytes, void* stream)
 {
+    return splitee_spectral_norm_probe(W, w_type, ldw, N, K, iters, seed, stream_id, sigma, history, workspace,
+                                       workspace_bytes, -1, nullptr, stream);
+}
+
+int splitee_spectral_norm_probe(const void* W, int w_type, int64_t ldw, int64_t N, int64_t K, int iters,
+                                uint64_t seed, uint64_t stream_id, double* sigma, double* history,
+                                void* workspace, size_t workspace_bytes, int64_t spins, int* path, void* stream)
+{
+    if (spins >= int64_t(1) << 32) return SPLITEE_ERR_ARG;
+    if (path) *path = SPLITEE_PATH_NONE;
     if (!valid_dtype(w_type)) return SPLITEE_ERR_DTYPE;
     if (w_type == SPLITEE_BF16_TILED) return SPLITEE_ERR_UNSUPPORTED;
     if (iters < 1 || iters > MAX_POWER_ITERS || !sigma) return SPLITEE_ERR_ARG;
@@ -545,7 +555,7 @@ int splitee_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int
         return SPLITEE_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) return SPLITEE_ERR_ALIGN;
     return splitee_host::launch_spectral_norm(W, w_type, ldw, N, K, iters, seed, stream_id, sigma, history,
-                                              workspace, as_stream(stream));
+                                              workspace, spins, path, as_stream(stream));
 }
 
 size_t splitee_sensitivity_workspace_bytes(void) { return 256; }

@@ -144,7 +144,7 @@ int launch_gemm_f64(const double* A, int64_t lda, const void* W, int w_type, int
 size_t spectral_workspace_bytes(int64_t N, int64_t K, int iters);
 int spectral_max_k();
 int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int64_t K, int iters, uint64_t seed,
-                         uint64_t sid, double* sigma, double* history, void* ws, hipStream_t s);
+                         uint64_t sid, double* sigma, double* history, void* ws, int64_t spins, int* path, hipStream_t s);
 int launch_vec_norms(const float* alpha, const float* beta, int64_t d, double* out_dev, double* out_host,
                      hipStream_t s);
 }  // namespace splitee_host

@@ -17,6 +17,7 @@
 #include <math.h>
 
 #include "common.hpp"
+#include "splitee_probe.h"
 
 namespace {
 
@@ -389,8 +390,8 @@ __global__ void __launch_bounds__(PI_NT) vec_norms_kernel(const float* __restric
 //    own columns (two buffers in turn; a workgroup empties its block of the one just used);
 //  - the dot products are summed over the wave by lane swaps and rotations in registers (through LDS they
 //    took 5 us of a round).
-// The launch is cooperative (every workgroup resident); a poll gives up after PI_SPINS tries all the same,
-// and the host then runs the rounds with W streamed.
+// The launch is cooperative (every workgroup resident); a poll gives up after PI_SPINS tries all the same (some
+// seconds), and the host then runs the rounds with W streamed.
 //
 // Parts, flags and z are read and written with agent scope (sc1: written through and read past the
 // XCDs' caches).  A partial row is rewritten after its workgroup read the next z, which exists
@@ -411,6 +412,7 @@ struct PxArgs {
     const void* W; int64_t ldw; int N, K, iters;
     float* z[2]; float* zpart; double* upart; double* sig;
     unsigned* flags; // PX_MAX_WGS flags, then the error word
+    unsigned spins;  // tries of a poll
 };
 
 template <bool WBF16> struct W4;
@@ -486,14 +488,14 @@ __device__ __forceinline__ double px_wave_sum(double v)
     return v;
 }
 
-// Every workgroup's flag has reached `round`; false (in all threads) after PI_SPINS tries.
-__device__ __forceinline__ bool px_wait(unsigned* flags, int G, unsigned round, unsigned* err)
+// Every workgroup's flag has reached `round`; false (in all threads) if it has not after `spins` tries.
+__device__ __forceinline__ bool px_wait(unsigned* flags, int G, unsigned round, unsigned spins, unsigned* err)
 {
     bool ok = true;
     if ((int)threadIdx.x < G) {
         unsigned n = 0;
         while (__hip_atomic_load(flags + threadIdx.x * PX_FLAG, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < round)
-            if (++n == PI_SPINS) {
+            if (++n >= spins) {
                 ok = false;
                 __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
@@ -561,7 +563,7 @@ __global__ void __launch_bounds__(PX_NT) pi_resident_kernel(PxArgs a)
                 }
             }
             if (full) break;
-            if (n == PI_SPINS) {
+            if (n >= a.spins) {
                 ok = false;
                 __hip_atomic_store(err, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 break;
@@ -644,7 +646,7 @@ __global__ void __launch_bounds__(PX_NT) pi_resident_kernel(PxArgs a)
             }
         }
         px_signal(flags + b * PX_FLAG, round);
-        if (!px_wait(flags, G, round, err)) return;
+        if (!px_wait(flags, G, round, a.spins, err)) return;
         if (b == 0 && wave == PX_NW - 1) { // sigma = ||u||
             double s = 0.0;
             for (int i = lane; i < G; i += WAVE) s += __hip_atomic_load(a.upart + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -773,24 +775,28 @@ void launch_round(const void* W, bool bf16, int64_t ldw, int N, int K, const PiL
                            (const float*)L.z, (const double*)L.zn_part, nzn, L.upart, L.zpart);
 }
 
-// All rounds in one cooperative launch; false if the device cannot hold it (nothing was enqueued).
+// All rounds in one cooperative launch.
 template <int CH, int RB, bool WBF16>
-bool launch_resident(const PxArgs& a, int G, hipStream_t s)
+hipError_t launch_resident(const PxArgs& a, int G, hipStream_t s)
 {
     const int q4 = (a.K / 4 + G - 1) / G;
     PxArgs args = a;
     void* kp[] = {&args};
-    if (hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&pi_resident_kernel<CH, RB, WBF16>), dim3((unsigned)G), dim3(PX_NT), kp,
-                                   (unsigned)((size_t)G * q4 * 16), s) == hipSuccess)
-        return true;
-    (void)hipGetLastError();
-    return false;
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(&pi_resident_kernel<CH, RB, WBF16>), dim3((unsigned)G), dim3(PX_NT), kp,
+                                      (unsigned)((size_t)G * q4 * 16), s);
 }
 
-bool run_resident(const PxArgs& a, int rb, bool bf16, hipStream_t s)
+// The device (a partition, say) cannot hold the workgroups together: nothing was enqueued.
+bool px_refused(hipError_t e)
+{
+    return e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported || e == hipErrorLaunchOutOfResources ||
+           e == hipErrorInvalidConfiguration;
+}
+
+hipError_t run_resident(const PxArgs& a, int rb, bool bf16, hipStream_t s)
 {
     const int ch = (a.K + PX_CW - 1) / PX_CW, G = (a.N + rb - 1) / rb;
-#define PX(CH, RB) case CH * 100 + RB: return bf16 ? launch_resident<CH, RB, true>(a, G, s) : false
+#define PX(CH, RB) case CH * 100 + RB: return bf16 ? launch_resident<CH, RB, true>(a, G, s) : hipErrorNotSupported
 #define PXF(CH, RB) case CH * 100 + RB: return bf16 ? launch_resident<CH, RB, true>(a, G, s) : launch_resident<CH, RB, false>(a, G, s)
     switch (ch * 100 + rb) {
     PXF(1, 4); PXF(1, 8); PXF(1, 16); PX(1, 24); PX(1, 32); PX(1, 40);
@@ -798,7 +804,7 @@ bool run_resident(const PxArgs& a, int rb, bool bf16, hipStream_t s)
     PXF(2, 4); PXF(2, 8); PX(2, 12); PX(2, 16); PX(2, 20);
     PXF(3, 4); PX(3, 8); PX(3, 12);
     PXF(4, 4); PX(4, 8);
-    default: return false;
+    default: return hipErrorNotSupported;
     }
 #undef PX
 #undef PXF
@@ -817,9 +823,9 @@ size_t spectral_workspace_bytes(int64_t N, int64_t K, int iters)
 }
 
 // The rounds and their results on the host, W resident (rb rows per workgroup) or streamed (rb 0).
-// *gave_up: the resident kernel's workgroups did not run together.
+// *path: what ran.
 static int power_rounds(const void* W, bool bf16, int64_t ldw, int64_t N, int64_t K, int iters, uint64_t seed,
-                        uint64_t sid, double* sigma, double* history, void* ws, int rb, bool* gave_up, hipStream_t s)
+                        uint64_t sid, double* sigma, double* history, void* ws, int rb, unsigned spins, int* path, hipStream_t s)
 {
     const PiLayout L = pi_layout(ws, N, K, iters, bf16);
     const int nwg = (int)pi_workgroups(N, K, bf16), nzn = (int)((K + PR_CB - 1) / PR_CB);
@@ -835,7 +841,14 @@ static int power_rounds(const void* W, bool bf16, int64_t ldw, int64_t N, int64_
     if (rb) {
         hipLaunchKernelGGL(px_clear_kernel, dim3(64), dim3(PI_NT), 0, s, L.flags, PX_MAX_WGS * PX_FLAG + 1,
                            reinterpret_cast<unsigned*>(L.z + L.zstride), (int)K);
-        resident = run_resident(PxArgs{W, ldw, (int)N, (int)K, iters, {L.z, L.z + L.zstride}, L.zpart, L.upart, L.sig, L.flags}, rb, bf16, s);
+        if (hipGetLastError() != hipSuccess) return SPLITEE_ERR_HIP; // of the launches so far
+        const hipError_t e = run_resident(
+            PxArgs{W, ldw, (int)N, (int)K, iters, {L.z, L.z + L.zstride}, L.zpart, L.upart, L.sig, L.flags, spins}, rb, bf16, s);
+        resident = e == hipSuccess;
+        if (!resident) {
+            (void)hipGetLastError(); // a refusal is no error of this call
+            if (!px_refused(e)) return SPLITEE_ERR_HIP;
+        }
     }
     for (int it = 0; it < iters && !resident; ++it) {
         switch (ch) {
@@ -861,22 +874,22 @@ static int power_rounds(const void* W, bool bf16, int64_t ldw, int64_t N, int64_
     if (resident && hipMemcpyAsync(&px_err, L.flags + PX_MAX_WGS * PX_FLAG, sizeof(px_err), hipMemcpyDeviceToHost, s) != hipSuccess)
         return SPLITEE_ERR_HIP;
     if (hipStreamSynchronize(s) != hipSuccess) return SPLITEE_ERR_HIP;
-    *gave_up = px_err != 0;
+    *path = !resident ? SPLITEE_PATH_STREAMED : px_err ? SPLITEE_PATH_GAVE_UP : SPLITEE_PATH_RESIDENT;
     return SPLITEE_OK;
 }
 
 int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int64_t K, int iters, uint64_t seed,
-                         uint64_t sid, double* sigma, double* history, void* ws, hipStream_t s)
+                         uint64_t sid, double* sigma, double* history, void* ws, int64_t spins, int* path, hipStream_t s)
 {
     const bool bf16 = w_type == SPLITEE_BF16;
-    bool gave_up = false;
+    int ran = SPLITEE_PATH_STREAMED, again;
     int rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, px_pays(N, K, iters) ? px_rows(N, K, bf16) : 0,
-                          &gave_up, s);
-    if (rc == SPLITEE_OK && gave_up)
-        rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, 0, &gave_up, s);
+                          spins < 0 ? PI_SPINS : (unsigned)spins, &ran, s);
+    if (rc == SPLITEE_OK && ran == SPLITEE_PATH_GAVE_UP)
+        rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, 0, 0, &again, s);
+    if (path) *path = ran;
     return rc;
 }
-
 
 int launch_vec_norms(const float* alpha, const float* beta, int64_t d, double* out_dev, double* out_host,
                      hipStream_t s)

@@ -189,6 +189,19 @@ def test_spectral_norm_of_empty_matrix_is_zero(lib):
         assert (rc, s, list(hist)) == (OK, 0.0, [0.0, 0.0, 0.0])
 
 
+def test_spectral_norm_probe_validation(lib):
+    s, path = ctypes.c_double(-1.0), ctypes.c_int(9)
+
+    def call(N=4, iters=3, spins=-1, p=ctypes.byref(path)):
+        return lib.splitee_spectral_norm_probe(P, BF16, 8, N, 8, iters, 0, 0, ctypes.byref(s), None, 256, 1 << 20, spins,
+                                               p, None)
+
+    assert call(spins=1 << 32) == ARG
+    assert call(iters=0) == ARG and path.value == sp.SPLITEE_PATH_NONE
+    assert call(N=0) == OK and path.value == sp.SPLITEE_PATH_NONE and s.value == 0.0
+    assert call(N=0, p=None) == OK
+
+
 def test_spectral_norm_workspace_size(lib):
     q = lib.splitee_spectral_norm_workspace_bytes
     assert q(8, 8, 0) == 0 and q(-1, 8, 1) == 0
