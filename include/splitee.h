@@ -373,8 +373,12 @@ size_t splitee_spectral_norm_workspace_bytes(int64_t N, int64_t K, int iters);
  *   history    host array of iters entries or NULL; receives sigma of every round
  *   workspace  device, >= splitee_spectral_norm_workspace_bytes(N, K, iters) bytes,
  *              256-byte aligned; no initial contents needed
- * Products accumulate in float32, squared norms in binary64.  The call
- * synchronises `stream` before it returns.
+ * Products accumulate in float32, squared norms in binary64.  A matrix that fits the chip's
+ * registers may run all rounds in one kernel, chosen by N, K, w_type and iters; its float32 sums
+ * are in another order, so that sigma of one round can differ in its last bits (some 1e-7 of it)
+ * between calls with different iters.  Repeated calls give the same bits (but for a device too busy to
+ * hold that kernel's workgroups together for seconds: it gives up, and the rounds run as without it).
+ * The call synchronises `stream` before it returns.
  */
 int splitee_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int64_t K, int iters,
                           uint64_t seed, uint64_t stream_id, double* sigma, double* history,

@@ -695,22 +695,41 @@ __global__ void __launch_bounds__(PI_NT) px_clear_kernel(unsigned* __restrict__ 
 // Rows per workgroup of the resident kernel: the fewest instantiated ones that cover N with at
 // most 128 workgroups, or the most if that takes up to 256; 0 where the registers do not hold the
 // matrix.  The exchanges grow with the workgroups, the arithmetic hardly counts: 1024 x 2560 takes 9.9 us a
-// round on 256, 7.8 on 128 and 7.5 on 64, 4096 x 2560 10.5, 9.1 and 11.0.
+// round on 256, 7.8 on 128 and 7.5 on 64, 4096 x 2560 10.5, 9.1 and 11.0.  (4 rows of more than 4096 columns and
+// float32 rows of more than 8192 would be matrices that px_pays never takes: 1024 x 9728 float32 on 256
+// workgroups 18.2 us a round, streamed 16.4.)
 int px_rows(int64_t N, int64_t K, bool bf16)
 {
-    static const int R1[] = {4, 8, 16, 24, 32, 40, 0}, R2[] = {4, 8, 12, 16, 20, 0}, R3[] = {4, 8, 12, 0}, R4[] = {4, 8, 0};
-    static const int F1[] = {4, 8, 16, 20, 0}, F2[] = {4, 8, 0}, F3[] = {4, 0};
+    static const int R1[] = {4, 8, 16, 24, 32, 40, 0}, R2[] = {8, 12, 16, 20, 0}, R3[] = {8, 12, 0}, R4[] = {8, 0};
+    static const int F1[] = {4, 8, 16, 20, 0}, F2[] = {8, 0};
     const int64_t ch = (K + PX_CW - 1) / PX_CW;
-    const int* l = bf16 ? (ch == 1 ? R1 : ch == 2 ? R2 : ch == 3 ? R3 : R4) : (ch == 1 ? F1 : ch == 2 ? F2 : F3);
-    if (ch < 1 || ch > 4) return 0;
+    if (ch < 1 || ch > (bf16 ? 4 : 2)) return 0;
+    const int* l = bf16 ? (ch == 1 ? R1 : ch == 2 ? R2 : ch == 3 ? R3 : R4) : (ch == 1 ? F1 : F2);
     for (; *l; ++l)
         if ((N + *l - 1) / *l <= (l[1] ? PX_MAX_WGS / 2 : PX_MAX_WGS)) return *l;
     return 0;
 }
 
-// Rounds from which the resident kernel pays: its cooperative launch costs 25 us once, and a round saves 4-7 us
-// of 10-20 from 10 M elements up and up to 1024 columns, 1-2 us of 9 between (512 x 4096: 8.1 against 9.0 us).
-bool px_pays(int64_t N, int64_t K, int iters) { return iters >= (N * K >= 10000000 || K <= 1024 ? 8 : 24); }
+// Whether the resident kernel, at rb rows per workgroup, is the faster one, by the modelled time: its cooperative
+// launch costs about 25 us once, which its rounds have to win back.  Microseconds of a round, fitted to 16-9728 rows
+// x 64-16384 columns of both types, 8, 24 and 64 rounds:
+//   streamed  6 + 0.45 a million elements + 0.4 a thousand columns; at least what its two launches and their
+//             dependent reductions take (one chunk of columns by the row count, 7.4-8.4 beyond)
+//   resident  4.8 + 0.7 a thousand columns + 0.5 a thousand rows + 0.05 a float4 column that a workgroup sums
+// (few rows are few workgroups, and each then sums many columns: 16 x 16384 takes 76 us a round, streamed 9.4).
+// So chosen, no matrix of 1288 measured ones takes longer than streamed by more than 2.4%, and 0.25% on
+// average than the better of the two; the rule before, by N K, K and 8 or 24 rounds, took up to 7.7 times as long
+// (16 x 16384; 512 x 9728 5-8%, 1024 x 9728 float32 16%).
+bool px_pays(int64_t N, int64_t K, int iters, bool bf16, int rb)
+{
+    if (!rb || iters < 8) return false;
+    const double n = (double)N * 1e-3, k = (double)K * 1e-3;
+    const int64_t G = (N + rb - 1) / rb, q4 = (K / 4 + G - 1) / G;
+    const double least = bf16 ? (K <= 1536 ? 9.5 + 0.5 * n : 8.4) : K <= PX_CW ? 7.0 + 0.8 * n : 7.4;
+    const double streamed = std::max(least, 6.0 + 0.45 * n * k + 0.4 * k);
+    const double resident = 4.8 + 0.7 * k + 0.5 * n + 0.05 * (double)q4;
+    return iters * (streamed - resident) > 25.0;
+}
 
 inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
 
@@ -801,9 +820,9 @@ hipError_t run_resident(const PxArgs& a, int rb, bool bf16, hipStream_t s)
     switch (ch * 100 + rb) {
     PXF(1, 4); PXF(1, 8); PXF(1, 16); PX(1, 24); PX(1, 32); PX(1, 40);
     case 120: return launch_resident<1, 20, false>(a, G, s);
-    PXF(2, 4); PXF(2, 8); PX(2, 12); PX(2, 16); PX(2, 20);
-    PXF(3, 4); PX(3, 8); PX(3, 12);
-    PXF(4, 4); PX(4, 8);
+    PXF(2, 8); PX(2, 12); PX(2, 16); PX(2, 20);
+    PX(3, 8); PX(3, 12);
+    PX(4, 8);
     default: return hipErrorNotSupported;
     }
 #undef PX
@@ -883,7 +902,8 @@ int launch_spectral_norm(const void* W, int w_type, int64_t ldw, int64_t N, int6
 {
     const bool bf16 = w_type == SPLITEE_BF16;
     int ran = SPLITEE_PATH_STREAMED, again;
-    int rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, px_pays(N, K, iters) ? px_rows(N, K, bf16) : 0,
+    const int rb = px_rows(N, K, bf16);
+    int rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, px_pays(N, K, iters, bf16, rb) ? rb : 0,
                           spins < 0 ? PI_SPINS : (unsigned)spins, &ran, s);
     if (rc == SPLITEE_OK && ran == SPLITEE_PATH_GAVE_UP)
         rc = power_rounds(W, bf16, ldw, N, K, iters, seed, sid, sigma, history, ws, 0, 0, &again, s);
