@@ -20,6 +20,11 @@
 // bfloat16 W, Qwen3-4B: 333 tokens QKV 181 -> 92 us, O 124 -> 68, gate/up 357 -> 277 (120 TFLOP/s), Down
 // 268 -> 149; 1024 tokens Down 635 -> 389 (131 TFLOP/s); one token O 30.6 -> 10.6; 32 x 512 x 512 8.4 -> 6.1;
 // unsplit (splitee_masked_linear) 128 tokens Llama-3.2-3B Down 595 -> 80 us.
+//
+// K <= 128 under many tiles is bound by the stores of Out and by a workgroup's latency from first load to store,
+// which the ring's loads past K lengthen.  One chain then holds all of K, its sums need no second set of registers,
+// so 128 x 128 tiles fit (ONE): 2048 x 4096 x 64 22.8 -> 16.9 us (the former 128 x 128 tiles 17.6), 1280 x 19456 x
+// 32 34.9 -> 29.6 (29.2), 8192 x 1024 x 128 29.6 -> 26.7 (25.6).
 #include "gemm_dev.hpp"
 
 #include <algorithm>
@@ -32,7 +37,7 @@ constexpr int F_NT = F_NW * WAVE;
 constexpr int F_BK = 32;          // k of one stage: 128 bytes of an A row
 constexpr int F_CHAIN = 4;        // K tiles that one accumulator chain runs over at most
 constexpr int F_MAX_TM = 8;       // 16-row blocks of a tile
-constexpr int f32_max_tn(int tm) { return tm >= 4 && tm < 8 ? 2 : 1; } // 64-column blocks (128 x 128 would spill)
+constexpr int f32_max_tn(int tm) { return tm >= 4 && tm < 8 ? 2 : 1; } // 64-column blocks (128 x 128 would spill, but for ONE)
 
 __device__ __attribute__((aligned(16))) const float f32_zeros[4] = {0.f, 0.f, 0.f, 0.f};
 
@@ -56,7 +61,8 @@ constexpr int f32_stages(int tm, int tn, bool wbf16)
     return s < 2 ? 2 : s >= 6 ? 6 : s == 5 ? 4 : s;
 }
 
-template <int TM, int TN, bool WBF16>
+// ONE: K of at most F_CHAIN tiles, unsplit: acc is the result, and nothing past K is loaded.
+template <int TM, int TN, bool WBF16, bool ONE = false>
 __global__ void __launch_bounds__(F_NT, 2)
 gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict__ Wv, int64_t ldw,
                 const float* __restrict__ C, int64_t ldc, float* __restrict__ Out, int64_t ldo, int M, int N, int K,
@@ -112,6 +118,7 @@ gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict
     // the loads of relative K tile t into stage q (zeros past the split's end and the matrix)
     auto issue = [&](int t, auto sc) {
         constexpr int q = decltype(sc)::value;
+        if (ONE && t >= nk) return; // (every wait is then for all loads)
         const int k = t < nk ? t * F_BK : K; // past every row's end
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
@@ -197,7 +204,7 @@ gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict
         }
         __builtin_amdgcn_sched_group_barrier(0x008, 3 * TM * TN, 0);
         __builtin_amdgcn_sched_barrier(0);
-        wait_vmem<(S - 2) * (LA + LW)>();
+        wait_vmem<ONE ? 0 : (S - 2) * (LA + LW)>();
         __builtin_amdgcn_s_waitcnt((0 << 8) | (7 << 4) | 15 | (3 << 14)); // lgkmcnt(0): a1 is in
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
@@ -219,7 +226,8 @@ gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict
         __builtin_amdgcn_sched_barrier(0);
         widen_w();
     };
-    auto flush = [&]() {
+    auto flush = [&](bool end = false) {
+        if (ONE && !end) return;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -236,7 +244,7 @@ gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict
     if constexpr (S > 3) issue(3, F_IC(3));
     if constexpr (S > 4) issue(4, F_IC(4));
     if constexpr (S > 5) issue(5, F_IC(5));
-    wait_vmem<(S - 1) * (LA + LW)>();
+    wait_vmem<ONE ? 0 : (S - 1) * (LA + LW)>();
     __builtin_amdgcn_s_barrier();
     read_w(st[0]);
     read_a(st[0], 0, a0);
@@ -267,7 +275,7 @@ gemm_f32_kernel(const float* __restrict__ A, int64_t lda, const void* __restrict
     if constexpr (TURN > 5) if (t + 4 < nk) step(t + 4, F_IC(4 % S));
 #undef F_IC
     wait_vmem<0>(); // loads past the last tile (zeros) have landed before the workgroup ends
-    flush();
+    flush(true);
 
     if (!whole && part) { // float4 (i, j) of lane l at ((i TN + j) 64 + l): rows 4 (l / 16) .. + 3, column l % 16
         f32x4_t* mp = reinterpret_cast<f32x4_t*>(part) + ((int64_t)(b - nfull) * F_NW + wave) * (TM * TN * 64);
@@ -360,6 +368,19 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, bool allow_split)
     const int ktiles = (int)((K + F_BK - 1) / F_BK);
     const size_t xt = ((size_t)M * K * 4 + 255) / 256 * 256;
     F32Plan best{};
+    // K in one chain and 128 x 128 tiles that nearly fill one to three rounds of two per CU: their count decides.  512
+    // tiles, 2048 x 4096 x 64: 16.9 us, with the tiles below 22.8; 480 (3000 x 2560 x 64) 15.6 and 19.2; 1520 (1280 x
+    // 19456 x 32) 29.6 and 34.9.  But 288 (1100 x 4096 x 64) 15.0 and 12.1, 1064 (777 x 19456 x 64) 34.9 and 28.9,
+    // 4096 (16384 x 4096 x 64) 120 and 113.
+    const int64_t m128 = (M + 127) / 128, t128 = m128 * ((N + 127) / 128), r128 = (t128 + 511) / 512;
+    if (ktiles <= F_CHAIN && r128 >= 1 && r128 <= 3 && t128 * 10 >= r128 * 512 * 9) {
+        best.tm = 8;
+        best.tn = 2;
+        best.mtiles = (int)m128;
+        best.nfull = (int)t128;
+        best.ksplit = best.ktps = 1;
+        return best;
+    }
     double best_cost = -1.0;
     // (rows that one more 16-row block would only pad are not tried: the planning costs host time)
     for (int tm = 1; tm <= F_MAX_TM && 16 * (tm - 1) < M; ++tm)
@@ -413,6 +434,15 @@ int launch_gemm_f32(const float* A, int64_t lda, const void* W, int w_type, int6
     const dim3 grid((unsigned)(p.nfull + (int64_t)p.rem * p.ksplit));
     const dim3 g2((unsigned)(((int64_t)p.rem * p.tm * p.tn * 256 + 255) / 256));
     const bool bf16 = w_type == SPLITEE_BF16;
+    if (p.tm == 8 && p.tn == 2) {
+        if (bf16)
+            hipLaunchKernelGGL((gemm_f32_kernel<8, 2, true, true>), grid, dim3(F_NT), 0, s, A, lda, W, ldw, C, ldc, Out, ldo, (int)M,
+                               (int)N, (int)K, p.mtiles, p.nfull, p.ktps, p.rem, part);
+        else
+            hipLaunchKernelGGL((gemm_f32_kernel<8, 2, false, true>), grid, dim3(F_NT), 0, s, A, lda, W, ldw, C, ldc, Out, ldo, (int)M,
+                               (int)N, (int)K, p.mtiles, p.nfull, p.ktps, p.rem, part);
+        return hipGetLastError() == hipSuccess ? SPLITEE_OK : SPLITEE_ERR_HIP;
+    }
 #define F_RUN(TM, TN)                                                                                                  \
     do {                                                                                                               \
         if (bf16)                                                                                                      \
