@@ -341,8 +341,7 @@ int splitee_masked_linear(const void* Xt, int in_prec, int64_t ldxt, const void*
     if (!Xt || !W || !R) return SPLITEE_ERR_ARG;
     if (!aligned16(Xt) || !pitch16(ldxt, prec_elsize(in_prec)) || !aligned16(R) || !pitch16(ldr, 4))
         return SPLITEE_ERR_ALIGN;
-    return splitee_host::launch_gemm(Xt, in_prec, ldxt, M * ldxt, W, w_type, ldw, nullptr, 0, R, ldr, M,
-                                     N, K, nullptr, 0, as_stream(stream));
+    return splitee_host::launch_product(Xt, in_prec, ldxt, M * ldxt, W, w_type, ldw, R, ldr, M, N, K, as_stream(stream));
 }
 
 int splitee_unmask(const float* R, int64_t ldr, const float* C, int64_t ldc, float* Y, int64_t ldy,

@@ -107,6 +107,10 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_typ
 int launch_gemm(const void* A, int prec, int64_t lda, int64_t plane_stride, const void* W,
                 int w_type, int64_t ldw, const float* C, int64_t ldc, float* Out, int64_t ldo,
                 int64_t M, int64_t N, int64_t K, void* ws, size_t ws_bytes, hipStream_t s);
+// A . W^T without a workspace (splitee_masked_linear): the GEMV or the K-over-waves kernel at few rows, else
+// launch_gemm unsplit.
+int launch_product(const void* A, int prec, int64_t lda, int64_t plane_stride, const void* W, int w_type, int64_t ldw,
+                   float* Out, int64_t ldo, int64_t M, int64_t N, int64_t K, hipStream_t s);
 // Binary32 GEMM, A float32, W row-major float32 or bfloat16; ws null: K is not split.
 size_t f32_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K);
 int launch_gemm_f32(const float* A, int64_t lda, const void* W, int w_type, int64_t ldw, const float* C, int64_t ldc,
@@ -132,7 +136,7 @@ struct WsplitPlan {
 };
 WsplitPlan plan_wsplit(int64_t M, int64_t N, int prec, int w_type);
 int launch_wsplit(const void* A, int prec, int64_t lda, int64_t plane_stride, const void* W, int w_type, int64_t ldw,
-                  const float* C, int64_t ldc, float* Out, int64_t ldo, int64_t M, int64_t N, int64_t K, hipStream_t s);
+                  float* Out, int64_t ldo, int64_t M, int64_t N, int64_t K, hipStream_t s);
 // bfloat16 W (N x K, row-major) -> the tiled order (splitee_tile_weights).
 int launch_tile_weights(const uint16_t* W, int64_t ldw, int64_t N, int64_t K, uint16_t* Wt, hipStream_t s);
 // Binary64 GEMM Out = A W^T (- C), A binary64, W bf16 / f32, Out binary64 or rounded to binary32.

@@ -1680,6 +1680,28 @@ size_t gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int prec, int w_typ
     return prec == SPLITEE_PREC_F32 ? f32_gemm_workspace_bytes(M, N, K) : plan_stream(M, N, K, prec, w_type, true).part_bytes;
 }
 
+// The buffer loads address each operand with 31-bit byte offsets.
+static bool buffers_reach(int prec, int64_t lda, int64_t pstride, int w_type, int64_t ldw, int64_t M, int64_t N, int64_t K)
+{
+    const int64_t planes = prec == SPLITEE_PREC_BF16X3 ? 3 : 1;
+    const int64_t wbytes = w_type == SPLITEE_BF16_TILED ? (int64_t)splitee::tiled_weights_bytes(N, K) : N * ldw * 2;
+    return (planes - 1) * pstride * 2 + M * lda * 2 < (int64_t(1) << 31) && wbytes < (int64_t(1) << 31);
+}
+
+int launch_product(const void* A, int prec, int64_t lda, int64_t pstride, const void* W, int w_type, int64_t ldw, float* Out,
+                   int64_t ldo, int64_t M, int64_t N, int64_t K, hipStream_t s)
+{
+    if (M > 0 && M <= WSPLIT_MAX_M && N > 0 && prec != SPLITEE_PREC_F32 &&
+        buffers_reach(prec, lda, pstride, w_type, ldw, M, N, K)) {
+        const SkSrc src{reinterpret_cast<const uint16_t*>(A), lda, pstride, nullptr, 0, nullptr, 0};
+        if (M <= GV_MMAX && w_type == SPLITEE_BF16 && M * K * 4 <= 160 * 1024)
+            return launch_gemv<false>(src, prec, W, ldw, nullptr, 0, Out, ldo, M, N, K, s);
+        if (plan_wsplit(M, N, prec, w_type).cost < unsplit_cost(plan_stream(M, N, K, prec, w_type, false), prec))
+            return launch_wsplit(A, prec, lda, pstride, W, w_type, ldw, Out, ldo, M, N, K, s);
+    }
+    return launch_gemm(A, prec, lda, pstride, W, w_type, ldw, nullptr, 0, Out, ldo, M, N, K, nullptr, 0, s);
+}
+
 int launch_gemm(const void* A, int prec, int64_t lda, int64_t pstride, const void* W, int w_type,
                 int64_t ldw, const float* C, int64_t ldc, float* Out, int64_t ldo, int64_t M,
                 int64_t N, int64_t K, void* ws, size_t ws_bytes, hipStream_t s)
@@ -1695,19 +1717,7 @@ int launch_gemm(const void* A, int prec, int64_t lda, int64_t pstride, const voi
     const int m = (int)M, n = (int)N, k = (int)K;
     const uint16_t* a = reinterpret_cast<const uint16_t*>(A);
     const uint16_t* w = reinterpret_cast<const uint16_t*>(W);
-    // the buffer loads address each operand with 31-bit byte offsets
-    const int64_t planes = prec == SPLITEE_PREC_BF16X3 ? 3 : 1;
-    const int64_t wbytes = w_type == SPLITEE_BF16_TILED ? (int64_t)splitee::tiled_weights_bytes(N, K) : N * ldw * 2;
-    if ((planes - 1) * pstride * 2 + M * lda * 2 >= (int64_t(1) << 31) || wbytes >= (int64_t(1) << 31) ||
-        p.part_bytes >= (size_t(1) << 31))
-        return SPLITEE_ERR_UNSUPPORTED;
-    if (!allow_split) { // splitee_masked_linear: no workspace
-        const SkSrc src{a, lda, pstride, nullptr, 0, nullptr, 0};
-        if (M <= GV_MMAX && w_type == SPLITEE_BF16 && M * K * 4 <= 160 * 1024)
-            return launch_gemv<false>(src, prec, W, ldw, C, ldc, Out, ldo, M, N, K, s);
-        if (M <= WSPLIT_MAX_M && plan_wsplit(M, N, prec, w_type).cost < unsplit_cost(p, prec))
-            return launch_wsplit(A, prec, lda, pstride, W, w_type, ldw, C, ldc, Out, ldo, M, N, K, s);
-    }
+    if (!buffers_reach(prec, lda, pstride, w_type, ldw, M, N, K) || p.part_bytes >= (size_t(1) << 31)) return SPLITEE_ERR_UNSUPPORTED;
     float* pp = ws ? ws_partials(ws) : nullptr;
 #define ST_LAUNCH(NP, BM_, BN_, WGM_, D_, NW_, T_) hipLaunchKernelGGL((gemm_stream_kernel<NP, BM_, BN_, WGM_, D_, NW_, T_>), grid, dim3(NW_ * WAVE), 0, s, a, lda, pstride, w, ldw, C, ldc, Out, ldo, m, n, k, p.mtiles, p.ntiles, p.ksplit, p.kt_per_split, pp)
 #define ST_SUM(BM_, BN_, WGM_, WGN_) hipLaunchKernelGGL((stream_sum_kernel<BM_, BN_, WGM_, WGN_>), g2, dim3(256), 0, s, pp, p.ksplit, C, ldc, Out, ldo, m, n, p.mtiles, tiles)

@@ -1,7 +1,7 @@
 // bfloat16 MFMA GEMM for few tokens without a split of K over workgroups (gfx950):
 // splitee_masked_linear, the untrusted GPU's product, has no workspace for one.
 //
-//   Out = A . W^T (- C),  A as one or three bfloat16 planes, W row-major or tiled
+//   Out = A . W^T,  A as one or three bfloat16 planes, W row-major or tiled
 //
 // What bounds it: W read once from HBM, and the masked input, which every workgroup reads
 // whole from L2.  A 64-row tile per workgroup (the streamed kernel) leaves most of the chip
@@ -36,8 +36,7 @@ __device__ __forceinline__ unsigned char* ws_stage()
 template <int NPL, int TN, bool TILED>
 __global__ void __launch_bounds__(WS_NT)
 wsplit_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride, const uint16_t* __restrict__ W, int64_t ldw,
-              const float* __restrict__ C, int64_t ldc, float* __restrict__ Out, int64_t ldo, int M, int N, int K,
-              int mtiles)
+              float* __restrict__ Out, int64_t ldo, int M, int N, int K, int mtiles)
 {
     constexpr int BM = 16, BN = 16 * TN;
     constexpr int LA = NPL * BM / 8;    // 1 KB loads to LDS per wave and K tile (8 rows of 128 bytes each)
@@ -104,13 +103,6 @@ wsplit_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride, cons
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // the thread's output elements (tid, tid + 512, .. of the tile) and their corrections
-    float cv[EPT];
-#pragma unroll
-    for (int e = 0; e < EPT; ++e) {
-        const int f = tid + e * WS_NT, row = m0 + f / BN, col = n0 + f % BN;
-        cv[e] = C && f < BM * BN && row < M && col < N ? C[(int64_t)row * ldc + col] : 0.f;
-    }
 #pragma unroll
     for (int u = 0; u < R; ++u) issue(u, u);
 
@@ -149,7 +141,7 @@ wsplit_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride, cons
     if (g < ng) consume(0);
 
     // the waves' sums meet in LDS (in the first stage where it holds them: every wave is done
-    // with it) and are added in wave order
+    // with it) and are added in wave order; a thread adds elements tid, tid + 512, .. of the tile
     float* const red = reinterpret_cast<float*>(RB <= WS_NW * SB ? st0 : ws_stage<2, RB <= WS_NW * SB ? 16 : RB>());
     __syncthreads();
 #pragma unroll
@@ -166,7 +158,7 @@ wsplit_kernel(const uint16_t* __restrict__ A, int64_t lda, int64_t pstride, cons
         float y = red[(f / BN) * LDR + f % BN];
 #pragma unroll
         for (int v = 1; v < WS_NW; ++v) y += red[(v * BM + f / BN) * LDR + f % BN];
-        Out[(int64_t)row * ldo + col] = C ? y - cv[e] : y;
+        Out[(int64_t)row * ldo + col] = y;
     }
 }
 
@@ -195,7 +187,7 @@ WsplitPlan plan_wsplit(int64_t M, int64_t N, int prec, int w_type)
 }
 
 int launch_wsplit(const void* A, int prec, int64_t lda, int64_t pstride, const void* W, int w_type, int64_t ldw,
-                  const float* C, int64_t ldc, float* Out, int64_t ldo, int64_t M, int64_t N, int64_t K, hipStream_t s)
+                  float* Out, int64_t ldo, int64_t M, int64_t N, int64_t K, hipStream_t s)
 {
     const int tn = plan_wsplit(M, N, prec, w_type).tn;
     const int64_t mt = (M + 15) / 16, wgs = mt * ((N + 16 * tn - 1) / (16 * tn));
@@ -203,7 +195,7 @@ int launch_wsplit(const void* A, int prec, int64_t lda, int64_t pstride, const v
     const uint16_t *w = reinterpret_cast<const uint16_t*>(W), *a = reinterpret_cast<const uint16_t*>(A);
 #define WS(NP, TN_, T)                                                                                               \
     hipLaunchKernelGGL((wsplit_kernel<NP, TN_, T>), dim3((unsigned)wgs), dim3(WS_NT), 0, s, a, lda, pstride, w, ldw, \
-                       C, ldc, Out, ldo, (int)M, (int)N, (int)K, (int)mt)
+                       Out, ldo, (int)M, (int)N, (int)K, (int)mt)
 #define WS_TN(NP, T)                                                                       \
     switch (tn) {                                                                          \
     case 1: WS(NP, 1, T); break;                                                           \
