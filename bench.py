@@ -38,7 +38,8 @@ layer's correction banks for 2048 positions: created from the GPU corrections in
 files, then loaded as decode steps and as one batch); ``noise_scale`` (the offline
 noise-scale step of the same model: spectral norms of W_val, W_up, W_gate and W_down
 by the power method, the sensitivity bounds of Theorems 1-3 from them, and the time
-of one power-method round against the HBM roofline of reading W once).
+of one power-method round: against the HBM roofline of reading W where a round streams
+W, on its own where W stays in registers).
 """
 import argparse
 import json
@@ -571,6 +572,7 @@ def noise_scale_leg(torch, sp, WL, workload, iters):
     stream = torch.cuda.current_stream()
 
     def timed(W, n):
+        """The kernels that n rounds took (a splitee_spectral_path) and the microseconds of the fastest of three calls."""
         nbytes = sp.splitee_spectral_norm_workspace_bytes(W.shape[0], W.shape[1], n)
         ws = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
         ws = ws[(-ws.data_ptr()) % 256:][:nbytes]
@@ -578,29 +580,54 @@ def noise_scale_leg(torch, sp, WL, workload, iters):
         for _ in range(3):
             a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
             a.record(stream)
-            sp.splitee_spectral_norm(W, sp.SPLITEE_BF16, W.shape[1], W.shape[0], W.shape[1], n, 0, 0, ws,
-                                     nbytes, stream=stream)
+            path, _ = sp.splitee_spectral_norm_probe(W, sp.SPLITEE_BF16, W.shape[1], W.shape[0], W.shape[1], n, 0, 0, ws,
+                                                     nbytes, stream=stream)
             b.record(stream)
             b.synchronize()
             best = min(best, a.elapsed_time(b) * 1e3)
-        return best
+        return path, best
 
-    round_us, gbs = {}, {}
+    round_us, resident = {}, {}
     for k, W in Ws.items():
         timed(W, 5)
-        t = (timed(W, 60) - timed(W, 10)) / 50.0
-        round_us[k] = round(t, 2)
-        gbs[k] = round(W.numel() * 2 / (t * 1e-6) / 1e9, 1)
-    big = max(Ws, key=lambda k: Ws[k].numel())
+        path, t = norm_round(lambda n: timed(W, n))
+        round_us[k], resident[k] = round(t, 2), path == sp.SPLITEE_PATH_RESIDENT
     return {"model": model.name, "iters": iters, "sigma": {k: round(v, 6) for k, v in sig.items()},
             "delta": {k: float("%.6g" % v) for k, v in delta.items()},
             "round_us": round_us,
-            "roofline": {"bound": "hbm", "kernel": "power-method round, %s %dx%d bf16"
-                         % ((big,) + tuple(Ws[big].shape)),
-                         "achieved": gbs[big], "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                         "frac": round(gbs[big] / HBM_PEAK_GBS, 4),
-                         "bytes_per_round": {k: int(W.numel() * 2) for k, W in Ws.items()},
-                         "achieved_per_matrix": gbs}}
+            "roofline": norm_roofline({k: tuple(W.shape) for k, W in Ws.items()}, round_us, resident)}
+
+
+def norm_round(timed):
+    """(path, microseconds) of one round of the power method from timed(rounds) -> (path, microseconds of the call):
+    the difference of two calls that took the same kernels.  More rounds may run W held in registers
+    and fewer streamed, so where one doubling crosses over, the next does not."""
+    for n in (30, 60):
+        (p0, t0), (p1, t1) = timed(n), timed(2 * n)
+        if p0 == p1:
+            break
+    else:
+        raise RuntimeError("spectral norm: kernels change at %d and again at %d rounds" % (n, 2 * n))
+    return p0, (t1 - t0) / n
+
+
+def norm_roofline(shapes, round_us, resident):
+    """The power method's roofline record: of the largest matrix, and the rates of those that are streamed.  A streamed
+    round reads W from HBM; where W stays in registers it is read once a call, and a round is bound by the
+    latency of the workgroups' exchanges, so it has a time and no rate."""
+    wbytes = {k: 2 * n * d for k, (n, d) in shapes.items()}
+    gbs = {k: round(wbytes[k] / (round_us[k] * 1e-6) / 1e9, 1) for k in shapes if not resident[k]}
+    big = max(shapes, key=lambda k: wbytes[k])
+    name = "power-method round, %s %dx%d bf16, W %s" % ((big,) + shapes[big] + ("in registers" if resident[big] else "streamed",))
+    if resident[big]:
+        out = {"bound": "latency", "kernel": name, "achieved": round_us[big], "unit": "us/round", "bytes_per_call": wbytes[big]}
+    else:
+        out = {"bound": "hbm", "kernel": name, "achieved": gbs[big], "peak": HBM_PEAK_GBS, "unit": "GB/s",
+               "frac": round(gbs[big] / HBM_PEAK_GBS, 4)}
+    out["bytes_per_round"] = {k: wbytes[k] for k in gbs}
+    out["achieved_per_matrix"] = gbs
+    out["resident"] = sorted(k for k in shapes if resident[k])
+    return out
 
 
 def noise_bank_leg(torch, sp, WL, workload, rows=2048):

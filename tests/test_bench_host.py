@@ -89,3 +89,26 @@ def test_leg_summary_picks_the_dominant_launch_and_the_whole_step():
     assert droof["bound"] == "hbm" and droof["step"]["bound"] == "hbm"
     assert droof["achieved"] == round(dpath.gemm_bytes()[2] / 20e-6 / 1e9, 1)
     assert droof["step"]["noise_mask_share"] == round(30.0 / 1800.0, 4)
+
+
+def test_power_method_round_is_a_difference_of_like_calls():
+    # streamed below 50 rounds (10 us each), in registers from there (25 us once, 6 us each)
+    calls = []
+
+    def timed(n):
+        calls.append(n)
+        return (1, 50.0 + 10.0 * n) if n < 50 else (2, 75.0 + 6.0 * n)
+    assert bench.norm_round(timed) == (2, 6.0) and calls == [30, 60, 60, 120]
+    assert bench.norm_round(lambda n: (1, 50.0 + 10.0 * n)) == (1, 10.0)
+
+
+def test_power_method_roofline_counts_w_only_where_it_is_streamed():
+    shapes = {"w_val": (1024, 3072), "w_up": (8192, 3072), "w_down": (3072, 8192)}
+    us = {"w_val": 8.0, "w_up": 12.7, "w_down": 19.0}
+    r = bench.norm_roofline(shapes, us, {"w_val": False, "w_up": True, "w_down": True})
+    assert r["bound"] == "latency" and r["achieved"] == 12.7 and r["bytes_per_call"] == 2 * 8192 * 3072
+    assert "frac" not in r and "peak" not in r and r["resident"] == ["w_down", "w_up"]
+    assert r["bytes_per_round"] == {"w_val": 2 * 1024 * 3072} and r["achieved_per_matrix"] == {"w_val": 786.4}
+    r = bench.norm_roofline(shapes, us, dict.fromkeys(shapes, False))
+    assert r["bound"] == "hbm" and r["achieved"] == 3963.1 and r["unit"] == "GB/s"
+    assert r["frac"] == round(3963.1 / bench.HBM_PEAK_GBS, 4) and not r["resident"]
