@@ -1483,13 +1483,18 @@ Plan plan_stream(int64_t M, int64_t N, int64_t K, int prec, int w_type, bool all
     return p;
 }
 
-// Above this many rows the tiles of the streamed kernel outnumber the CUs on any projection.
+// Rows up to which the two costs decide between the streamed kernel unsplit and the K-over-waves kernel; they were
+// fitted there.  It is not where the two cross: above it too the streamed kernel's tiles leave CUs idle on narrow W.
+// Three planes, tiled W, at 129 and 256 rows, streamed and K-over-waves: 3072 x 8192 147, 43 and 147, 57 us; 5120 x 3072
+// 35, 26 and 36, 47; 16384 x 3072 63, 80 and 71, 139.
 constexpr int64_t WSPLIT_MAX_M = 128;
 
 // Microseconds per K tile of the streamed kernel with K unsplit: rounds of 256 workgroups
 // times a tile's time, to compare with plan_wsplit (both fitted to 4-64 tokens on the
 // Llama-3.2-3B and Qwen3-4B projections, tiled W: a 128-column tile takes 0.65-0.8 us with three
-// planes and 0.5 with one, a 256-column tile 1.0-1.1 and 0.8).
+// planes and 0.5 with one, a 256-column tile 1.0-1.1 and 0.8).  Row-major W has no constants of its own and
+// takes longer, 1.1-1.6 us a tile: the streamed kernel is then kept where the other is faster (5120 x 3072 at 96 rows
+// 69 us, K-over-waves 34; 16384 x 3072 at 64 rows 76, 66), never the reverse.
 double unsplit_cost(const Plan& p, int prec)
 {
     const double tile = (prec == SPLITEE_PREC_BF16X3 ? 1.05 : 0.8) * (p.bn >= 192 ? 1.0 : 0.7);
