@@ -1,8 +1,9 @@
-"""The power method with W held in registers, at the edges of its row and column steps.
+"""The power method around the steps of the kernel that holds W in registers.
 
 Row counts on both sides of each step of rows per workgroup, column counts on both sides of each
-4096-column chunk, one past the largest that fits (which streams W), a workgroup count that leaves some
-without columns to sum, the fewest rounds that run resident and one less.  Bars as in test_gpu_sensitivity.py.
+4096-column chunk, one past the largest that fits, a workgroup count that leaves some without columns to
+sum, few rounds and more.  Some run in registers and some streamed; test_gpu_norm_paths.py asserts which, and holds the
+registers' results to the same bars.  Bars as in test_gpu_sensitivity.py.
 """
 import numpy as np
 import pytest
