@@ -11,7 +11,8 @@
 //    by two reads less LDS and measured the same);
 //  - one barrier per K tile, in the middle of its MFMAs: the fragments of the next half tile are
 //    read under the MFMAs of this one.
-// The matrix cores are then busy 83% of the cycles, at 2.2 GHz.  An accumulator chain runs over 96 or 128 k
+// The matrix cores are then busy 77% of the cycles on gate/up at 333 tokens and 70-71% on the smaller
+// projections, at 2.2 GHz (profiles/counters_f32_qwen3-4b-m333.md).  An accumulator chain runs over 96 or 128 k
 // and is then added into a second set of registers, so the rounding error no longer grows with
 // K: 2.0e-7 to 2.5e-7 of the result at K = 9728 where one chain has 1.7e-6, and 8e-7 before (five splits).
 // Chains of 192 k lost to the former splits at K = 256-1024 (2.5e-7 against 2.1e-7, now 2.1e-7) and are
@@ -390,7 +391,8 @@ F32Plan plan_f32(int64_t M, int64_t N, int64_t K, bool allow_split)
             const double ktile = 0.121 * tm * tn + 0.06;
             for (int ks = 1; ks <= F_MAX_KS; ++ks) {
                 // a split has at least four K tiles, and partials and masked input fit the scratch of the
-                // call without a workspace
+                // call without a workspace, whose bits are those of the call with one (so nothing is split from about
+                // 1700 x 9728 up; 1800 and 2048 rows are faster there than with the former splits all the same)
                 if (ks > 1 && (!allow_split || rem == 0 || ktiles / ks < 4)) break;
                 const int ktps = ktiles > 0 ? (ktiles + ks - 1) / ks : 1;
                 if (ks > 1 && (ktiles + ktps - 1) / ktps != ks) continue;

@@ -16,7 +16,8 @@
 // straight to MFMA operand registers.  Two K tiles in flight; three were as fast or slower.
 //
 // 15 tokens, Llama-3.2-3B, tiled W, against the streamed kernel's unsplit tiles: QKV 31.9 ->
-// 12.5 us, O 31.4 -> 9.9, gate/up 47.5 -> 22.4 (4.5 TB/s of W), Down 76.3 -> 21.6; row-major W
+// 12.5 us, O 31.4 -> 9.9, gate/up 47.5 -> 22.4 (18.1 alone: 5.7 TB/s,
+// profiles/counters_product_llama3b-m15.md), Down 76.3 -> 21.6; row-major W
 // at 32 tokens 93 -> 19, 92 -> 14, 94 -> 46 and 204 -> 31 us.
 #include "gemm_dev.hpp"
 

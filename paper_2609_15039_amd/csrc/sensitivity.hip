@@ -398,7 +398,7 @@ __global__ void __launch_bounds__(PI_NT) vec_norms_kernel(const float* __restric
 // only after every workgroup read its parts.  A block of z is emptied when every flag says that
 // the round's z was read, and filled again a round later, behind the flags of that round.
 //
-// Llama-3.2-3B W_up (8192 x 3072 bfloat16): 21.0 -> 12.7 us a round; 1024 x 1024 10.9 -> 6.2, 1024 x 2560 9.3 -> 7.8.
+// Llama-3.2-3B W_up (8192 x 3072 bfloat16): 21.0 -> 10.4 us a round; 1024 x 1024 10.9 -> 6.2, 1024 x 2560 9.3 -> 7.8.
 constexpr int PX_NT = 1024;
 constexpr int PX_NW = PX_NT / WAVE;
 constexpr int PX_CW = 4 * PX_NT;          // columns of one register chunk
